@@ -75,7 +75,7 @@ def log(msg):
 # translation unit, the headers it includes and the build script's flags
 STEP_SOURCES = [os.path.join(ROOT, "paper_1010_4124_amd", "csrc", f) for f in
                 ("lbm_forward.hip", "lbm_device.h", "lbm_fast.h", "lbm_internal.h", "lbm_stage.h",
-                 "lbm_step.h")] + [os.path.join(ROOT, "include", "lbm.h"),
+                 "lbm_step.h", "lbm_tile.h")] + [os.path.join(ROOT, "include", "lbm.h"),
                                    os.path.join(ROOT, "paper_1010_4124_amd", "build.py")]
 
 
@@ -136,18 +136,21 @@ def read_traffic(kernel_name, pattern=None):
 def step_kernel_name(variant):
     """The step's kernel(s): a state-pass variant (M = 2) launches k_state and
     then the step kernel each step; both count as the step. The fast-tile
-    variants (M = 3) launch k_step_fast<R, W, D, NT>."""
+    variants (M = 3) launch k_step_fast<R, W, D, NT>, the whole-tile variants
+    (M = 0, G = 18) k_step_tile<R, NT>."""
     from paper_1010_4124_amd import lbm
     R, G, W, D, NT, M = lbm.lbm_step_variant_info(variant)
     nt = "true" if NT else "false"
     if M == 3:
         return f"lbmd::k_step_fast<{R}, {W}, {D}, {nt}>"
+    if M == 0 and G == 18:
+        return f"lbmd::k_step_tile<{R}, {nt}>"
     name = f"lbmd::k_step<{R}, {G}, {W}, {D}, {nt}, {M}>"
     return name + " + lbmd::k_state" if M == 2 else name
 
 
 def _is_step(name):
-    return "k_step<" in name or "k_step_fast<" in name
+    return "k_step<" in name or "k_step_fast<" in name or "k_step_tile<" in name
 
 
 # ---------------------------------------------------------------------------
@@ -565,8 +568,9 @@ def summarize_batch(trace, log_path, commands):
     rows = _table_rows(tab)
     ev = _bench_line(log_path, "batch")
     v = ev["variant"]
-    name = (f"lbmd::k_step_batch<{v[0]}, {v[1]}, {v[2]}, {v[3]}, "
-            f"{'true' if v[4] else 'false'}, {v[5]}>")
+    nt = "true" if v[4] else "false"
+    name = (f"lbmd::k_step_batch_tile<{v[0]}, {nt}>" if v[5] == 0 and v[1] == 18 else
+            f"lbmd::k_step_batch<{v[0]}, {v[1]}, {v[2]}, {v[3]}, {nt}, {v[5]}>")
     step_key = max((k for k in rows if k[0] == name), key=lambda k: int(rows[k][2]))
     red_key = next(k for k in rows if k[0] == "lbmd::k_reduce_batch")
     stp = float(rows[step_key][3])

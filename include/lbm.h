@@ -249,7 +249,11 @@ int lbm_sep_project(lbm_ctx* ctx, const double* g, const double* A, int32_t M, c
  * that bounds the register budget; D planes are prefetched ahead of the one
  * being computed; NT = 1 stores f^{n+1} with non-temporal stores. M says how
  * a tile obtains its moments (Eq. (10)):
- *   0  every (tile, group) workgroup sums the 19 planes of f^n itself;
+ *   0  every (tile, group) workgroup sums the 19 planes of f^n itself; with
+ *      G = 18 one workgroup of 12 wavefronts takes all velocities of a tile,
+ *      each plane read once (grids wider than 2^24 cells run the G = 3 kernel
+ *      instead; a batch launches one workgroup per work item whatever its
+ *      slots_per_xcd);
  *   1  the sums rho, j, E are carried from each step to the next (a call
  *      first forms them from f_in) and the G groups are the waves of one
  *      workgroup;

@@ -428,17 +428,29 @@ int lbm_get_step_variant(lbm_ctx* c, int32_t* v)
     return LBM_OK;
 }
 
-// Default step variant (the autotuner can override it per context or batch),
-// the fastest measured on MI355X: on small grids a state pass and one
-// velocity per workgroup; on large grids (or batches) carried moment sums
-// with the fast-tile kernel and non-temporal stores.
-int lbmi_default_variant(int nx, int ny) { return lbmi_default_variant_cells((int64_t)nx * ny); }
-
-int lbmi_default_variant_cells(int64_t cells)
+// Default step variant (the autotuner can override it per context or batch)
+// from the numbers of 64 x 1, 64 x 2 and 64 x 4 tiles (over all instances of a
+// batch), as measured on MI355X (microseconds per step, shear layers):
+//  - A whole-tile step takes the latency of one tile while all its workgroups
+//    are resident at once (two per CU: 512), less for lower tiles: 128^2 takes
+//    7.5 with R = 1 (256 tiles), 8.4 with R = 2, 10.8 with R = 4 (state pass and
+//    plane kernel: 12.2); 256^2 15.1, 11.5 (512 tiles), 11.7 (17.0).
+//  - Beyond that R = 4, which reads the fewest halo rows: 512^2 27.4 against
+//    32.2 with R = 2 and 37.0 for state pass and plane kernel.
+//  - The fast-tile kernel moves more bytes but keeps the chip busier. Its
+//    2048 wavefronts take the tiles in rounds, of about 40 us, and the band
+//    tiles at the grid's edge take 85 us: it wins from two full rounds on
+//    (1024^2: 97 against 102; 2048^2: 320 against 390; the 64-instance sweep
+//    of 20768 tiles: 480 against 565), unless the last round is nearly empty
+//    (1448^2, 4.07 rounds: 231 against 210; 1101 x 605, 1.3: 102 against 67).
+int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4)
 {
-    const bool large = cells >= (1ll << 21);
-    const int small_v[6] = {4, 18, 4, 1, 0, 2}, large_v[6] = {4, 1, 2, 1, 1, 3};
-    const int* want = large ? large_v : small_v;
+    constexpr int64_t RESIDENT = 512, ROUND = 2048;
+    const int64_t rounds = (t4 + ROUND - 1) / ROUND;
+    const bool fast = t4 >= 2 * ROUND && 100 * t4 >= 84 * ROUND * rounds;
+    const int R = t1 <= RESIDENT ? 1 : t2 <= RESIDENT ? 2 : 4;
+    const int tile_v[6] = {R, 18, 6, 1, 0, 0}, fast_v[6] = {4, 1, 2, 1, 1, 3};
+    const int* want = fast ? fast_v : tile_v;
     for (int v = 0; v < step_variant_count(); ++v) {
         int d[6];
         step_variant_desc(v, d);
@@ -447,6 +459,12 @@ int lbmi_default_variant_cells(int64_t cells)
         if (same) return v;
     }
     return 0;
+}
+
+int lbmi_default_variant(int nx, int ny)
+{
+    const int64_t tx = ((int64_t)nx + 63) / 64;
+    return lbmi_default_variant_tiles(tx * ny, tx * ((ny + 1) / 2), tx * (((int64_t)ny + 3) / 4));
 }
 
 static int adjoint_step(lbm_ctx* c, const double* f_n, const double* sums_n,

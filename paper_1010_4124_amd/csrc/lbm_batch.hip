@@ -30,6 +30,7 @@
 #include "lbm_internal.h"
 #include "lbm_stage.h"
 #include "lbm_step.h"
+#include "lbm_tile.h"
 
 namespace lbmd {
 
@@ -64,6 +65,27 @@ struct BatchArgs {
     Consts k;
 };
 
+__device__ __forceinline__ StepGrid inst_grid(const BatchArgs& a, const BatchInst& d)
+{
+    StepGrid s;
+    s.fin = a.fin + d.off;
+    s.fout = a.fout + d.off;
+    s.nx = d.nx;
+    s.ny = d.ny;
+    s.bc[0] = d.bc[0];
+    s.bc[1] = d.bc[1];
+    s.bc[2] = d.bc[2];
+    s.bc[3] = d.bc[3];
+    s.tiles_x = d.tiles_x;
+    s.ke_axis = d.ke_axis;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s.gb[q] = d.goff[q] >= 0 ? a.gbuf + d.goff[q] : nullptr;
+    s.cx = d.cx;
+    s.cy = d.cy;
+    s.ct = d.ct;
+    return s;
+}
+
 template <int R, int G, int W, int DEPTH, bool NT, int MODE>
 __global__ __launch_bounds__((64 * Waves<G, MODE>::N)) __attribute__((amdgpu_waves_per_eu(W)))
 void k_step_batch(BatchArgs a)
@@ -81,22 +103,7 @@ void k_step_batch(BatchArgs a)
     for (int w = lo + (b >> 3); w < hi; w += a.slots) {
         const int2 it = a.work[w];
         const BatchInst& d = a.inst[it.x];
-        StepGrid s;
-        s.fin = a.fin + d.off;
-        s.fout = a.fout + d.off;
-        s.nx = d.nx;
-        s.ny = d.ny;
-        s.bc[0] = d.bc[0];
-        s.bc[1] = d.bc[1];
-        s.bc[2] = d.bc[2];
-        s.bc[3] = d.bc[3];
-        s.tiles_x = d.tiles_x;
-        s.ke_axis = d.ke_axis;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) s.gb[q] = d.goff[q] >= 0 ? a.gbuf + d.goff[q] : nullptr;
-        s.cx = d.cx;
-        s.cy = d.cy;
-        s.ct = d.ct;
+        const StepGrid s = inst_grid(a, d);
         constexpr int GW = ML == PH_CARRY ? 1 : G;
         const int tile = it.y / GW, grp = it.y - tile * GW;
         double* ke = a.ke_part ? a.ke_part + 2 * ((int64_t)d.ke_off + tile) : nullptr;
@@ -114,6 +121,48 @@ void k_step_batch(BatchArgs a)
                                        ML == PH_CARRY ? a.m_out + d.moff : nullptr);
         __syncthreads();  // LDS is reused by the next item
     }
+}
+
+// The whole-tile variants (lbm_tile.h): work items are tiles. One item, as
+// tile_step sees it: the instance's descriptor is read where it is used.
+struct TileOfBatch {
+    const BatchArgs& a;
+    const BatchInst* d;
+    int x0, y0;
+    double* ke;
+    __device__ int nx() const { return d->nx; }
+    __device__ int ny() const { return d->ny; }
+    __device__ const double* fin() const { return a.fin + d->off; }
+    __device__ double* fout() const { return a.fout + d->off; }
+    __device__ double cx() const { return d->cx; }
+    __device__ double cy() const { return d->cy; }
+    __device__ double ct() const { return d->ct; }
+    __device__ int ke_axis() const { return d->ke_axis; }
+    __device__ GridBC bc() const { return grid_bc(inst_grid(a, *d)); }
+    __device__ double side_eq(const TileConsts&, int side, int i) const
+    {
+        return d->side_eq[side * NV + i];
+    }
+};
+
+template <int R, bool NT>
+__global__ __launch_bounds__((64 * TILE_WAVES)) __attribute__((amdgpu_waves_per_eu(6)))
+void k_step_batch_tile(BatchArgs a, TileConsts k)
+{
+    __shared__ double lds[TileWg<R>::LDS];
+
+    const int b = blockIdx.x;
+    const int work = (b & 7) * a.per_xcd + (b >> 3);
+    if (work >= a.nwork) return;
+    const int2 it = a.work[work];
+    const BatchInst* d = a.inst + it.x;
+    const int ty = it.y / d->tiles_x, tx = it.y - ty * d->tiles_x;
+    const TileOfBatch g{a, d, tx * TX, ty * R,
+                        a.ke_part ? a.ke_part + 2 * ((int64_t)d->ke_off + it.y) : nullptr};
+    if (fast_tile(g.bc(), g.x0, g.y0, TX, R, HALO))
+        tile_step<R, NT, true>(g, k, lds);
+    else
+        tile_step<R, NT, false>(g, k, lds);
 }
 
 // Per-instance reduction of the tile partials: block i writes
@@ -187,13 +236,27 @@ __global__ __launch_bounds__(256) void k_reduce_batch(const double* __restrict__
 struct BatchVariant {
     int R, G, M;
     void (*kernel)(BatchArgs);
+    void (*tile)(BatchArgs, TileConsts);
+    // work items per tile: the velocity groups, unless they share a workgroup
+    int items() const { return M == PH_CARRY || M == PH_TILE ? 1 : G; }
+};
+template <int R, int G, int WB, int D, bool NT, int M>
+struct BatchKernel {
+    static constexpr void (*fn)(BatchArgs) = k_step_batch<R, G, WB, D, NT, M>;
+    static constexpr void (*tile)(BatchArgs, TileConsts) = nullptr;
+};
+template <int R, int G, int WB, int D, bool NT>
+struct BatchKernel<R, G, WB, D, NT, PH_TILE> {
+    static constexpr void (*fn)(BatchArgs) = nullptr;
+    static constexpr void (*tile)(BatchArgs, TileConsts) = k_step_batch_tile<R, NT>;
 };
 // The batched kernel keeps an instance descriptor live as well and takes the
 // variant's own batch wave target WB, chosen so that it does not spill. The
 // host side treats the fast-tile variants (M = 3) as carried-moment ones:
 // same work items, sums and buffers.
 #define LBM_BATCH_VARIANT(R, G, W, D, NT, M, WB) \
-    {R, G, (M == PH_FAST ? PH_CARRY : M), k_step_batch<R, G, WB, D, NT, M>},
+    {R, G, (M == PH_FAST ? PH_CARRY : M), BatchKernel<R, G, WB, D, NT, M>::fn,                   \
+     BatchKernel<R, G, WB, D, NT, M>::tile},
 static const BatchVariant kBatchVariants[] = {LBM_STEP_VARIANTS(LBM_BATCH_VARIANT)};
 #undef LBM_BATCH_VARIANT
 
@@ -278,11 +341,20 @@ void drop_graphs(lbm_batch* b)
     b->graphs.clear();
 }
 
+// The kernel of the current variant (its stand-in if an instance is wider than
+// that kernel takes).
+const BatchVariant& batch_kernel(const lbm_batch* b)
+{
+    int nx = 0;
+    for (const BatchInst& d : b->hinst) nx = std::max(nx, d.nx);
+    return kBatchVariants[step_variant_for(b->variant, nx)];
+}
+
 // Tile counts, descriptor table and work list for the current variant.
 int build_tables(lbm_batch* b)
 {
-    const BatchVariant& V = kBatchVariants[b->variant];
-    const int per_tile = V.M == PH_CARRY ? 1 : V.G;  // work items per tile
+    const BatchVariant& V = batch_kernel(b);
+    const int per_tile = V.items();
     int64_t nwork = 0, ntiles = 0, nblk = 0;
     for (int i = 0; i < b->n; ++i) {
         BatchInst& d = b->hinst[i];
@@ -319,7 +391,7 @@ hipError_t launch_batch_step(lbm_batch* b, const double* src, double* dst, bool 
                              hipStream_t st, int row = 0)
 {
     double* part = b->ke_part + 2 * (int64_t)b->ke_cap * row;
-    const BatchVariant& V = kBatchVariants[b->variant];
+    const BatchVariant& V = batch_kernel(b);
     // outflow ghosts of the state this step starts from, all instances at
     // once (with a state pass, that pass writes them)
     if (b->noflow > 0 && V.M != PH_STATE) {
@@ -353,6 +425,11 @@ hipError_t launch_batch_step(lbm_batch* b, const double* src, double* dst, bool 
     a.per_xcd = (b->nwork + 7) / 8;
     a.slots = b->slots > 0 ? std::min(b->slots, a.per_xcd) : a.per_xcd;
     a.k = b->k;
+    if (V.M == PH_TILE) {
+        hipLaunchKernelGGL(V.tile, dim3(8 * a.per_xcd), dim3(64 * TILE_WAVES), 0, st, a,
+                           tile_consts(b->k));
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(V.kernel, dim3(8 * a.slots), dim3(64 * (V.M == PH_CARRY ? V.G : 1)), 0, st,
                        a);
     return hipGetLastError();
@@ -495,7 +572,7 @@ static int batch_create_impl(const lbm_params* inst, int32_t n, const int64_t* f
             const int64_t nt = (int64_t)((inst[i].nx + TX - 1) / TX) *
                                ((inst[i].ny + kBatchVariants[v].R - 1) / kBatchVariants[v].R);
             t += nt;
-            w += nt * (kBatchVariants[v].M == PH_CARRY ? 1 : kBatchVariants[v].G);
+            w += nt * kBatchVariants[v].items();
         }
         wmax = std::max(wmax, w);
         tmax = std::max(tmax, t);
@@ -589,7 +666,11 @@ static int batch_create_impl(const lbm_params* inst, int32_t n, const int64_t* f
         bhip(e, "batch block lists");
         return LBM_ENOMEM;
     }
-    b->variant = lbmi_default_variant_cells(b->cells);
+    int64_t t[3] = {0, 0, 0};  // tiles of 64 x 1, 2 and 4 cells
+    for (int i = 0; i < n; ++i)
+        for (int q = 0; q < 3; ++q)
+            t[q] += (int64_t)((inst[i].nx + TX - 1) / TX) * ((inst[i].ny + (1 << q) - 1) >> q);
+    b->variant = lbmi_default_variant_tiles(t[0], t[1], t[2]);
     const int rc = build_tables(b);
     if (rc) {
         lbm_batch_destroy(b);

@@ -28,13 +28,16 @@ struct lbm_ctx {
 int lbmi_validate(const lbm_params* p);
 void lbmi_fill_consts(const lbm_params* p, lbmd::Consts* h);
 int lbmi_default_variant(int nx, int ny);
-int lbmi_default_variant_cells(int64_t cells);
+int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4);
 int lbmi_default_adj_variant(int64_t cells);
 void lbmi_set_error(const char* msg);
 
 namespace lbmd {
 int step_variant_count();
 int step_variant_desc(int v, int info[6]);
+// the variant that a step of a grid nx cells wide launches: `variant`, or its
+// stand-in where that kernel does not take grids so wide
+int step_variant_for(int variant, int nx);
 int step_ntiles(int variant, int nx, int ny);
 hipError_t launch_step(int variant, const double* fin, double* fout, const Consts& k,
                        double* ke_part, int nx, int ny, const int bc[4], double cx, double cy,

@@ -226,6 +226,8 @@ enum {
     PH_CARRY = 1,  // read the sums rho, j, E the previous step wrote
     PH_STATE = 2,  // read the cell state (dt/tau rho, T, u/T, v/T) a state pass wrote
     PH_FAST = 3,   // carried sums as PH_CARRY; fast tiles by the kernel of lbm_fast.h
+    PH_TILE = 4,   // sum the 19 planes as PH_SUMS, by one workgroup that holds the whole tile
+                   // (lbm_tile.h)
 };
 
 // Waves per workgroup of a variant: the G groups are waves of one workgroup
@@ -614,7 +616,10 @@ __device__ __forceinline__ void step_work(const StepGrid& a, const Consts& k, SE
 // register budget (a lower target) for the same variant. Both the
 // single-grid and the batched kernel are instantiated for every entry, in
 // this order. No kernel may spill registers to scratch memory (the build
-// refuses one that does): the targets are chosen so that none does.
+// refuses one that does): the targets are chosen so that none does. The
+// PH_TILE entries (reported as M = 0 with G = 18: they sum the planes of f^n
+// themselves, every velocity of a tile in one workgroup) always have a target
+// of 6 wavefronts per SIMD, two workgroups of 12 per CU.
 #define LBM_STEP_VARIANTS(X)                                                                     \
     X(4, 1, 3, 1, 0, 0, 2) X(4, 3, 3, 1, 0, 0, 2) X(8, 2, 2, 1, 0, 0, 1)                         \
     X(8, 1, 2, 1, 0, 0, 1) X(2, 3, 4, 1, 0, 0, 3) X(8, 2, 2, 1, 1, 0, 1)                         \
@@ -623,6 +628,8 @@ __device__ __forceinline__ void step_work(const StepGrid& a, const Consts& k, SE
     X(2, 18, 5, 1, 0, 2, 4) X(4, 3, 3, 1, 0, 2, 3)                                               \
     X(2, 9, 4, 1, 0, 2, 3) X(2, 6, 4, 1, 0, 2, 3) X(4, 9, 3, 1, 0, 2, 3)                         \
     X(4, 6, 3, 1, 0, 2, 3) X(2, 1, 3, 1, 1, 1, 3) X(2, 1, 3, 1, 0, 1, 3)                         \
-    X(4, 1, 2, 1, 1, 3, 2) X(4, 1, 2, 2, 1, 3, 2) X(4, 1, 2, 1, 0, 3, 2)
+    X(4, 1, 2, 1, 1, 3, 2) X(4, 1, 2, 2, 1, 3, 2) X(4, 1, 2, 1, 0, 3, 2)                         \
+    X(4, 18, 6, 1, 0, 4, 6) X(4, 18, 6, 1, 1, 4, 6) X(2, 18, 6, 1, 0, 4, 6)                      \
+    X(1, 18, 6, 1, 0, 4, 6)
 
 }  // namespace lbmd
