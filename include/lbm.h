@@ -114,8 +114,8 @@ int lbm_init(lbm_ctx* ctx, const double* rho, const double* ux, const double* uy
 /* Advance nsteps >= 1 forward-Euler steps (Eq. (47)) from f_in; the result
  * lands in f_out and f_in is left unchanged. Each step computes, per cell,
  * the moments of Eq. (10) from f, f^eq, the flux differences of every
- * velocity along x and y (WENO5, or the upwind scheme that p.scheme names:
- * one thread per cell, a plain comparison kernel) and the BGK relaxation.
+ * velocity along x and y (WENO5, or the upwind scheme that p.scheme names)
+ * and the BGK relaxation.
  * ke_log: NULL, or device double[2*nsteps] receiving for each step n the
  * transverse kinetic energy of the state the step starts from,
  * ke_log[2n] = sum_cells rho u_n^2 / 2 * dx * dy and ke_log[2n+1] =
@@ -251,9 +251,8 @@ int lbm_sep_project(lbm_ctx* ctx, const double* g, const double* A, int32_t M, c
  * a tile obtains its moments (Eq. (10)):
  *   0  every (tile, group) workgroup sums the 19 planes of f^n itself; with
  *      G = 18 one workgroup of 12 wavefronts takes all velocities of a tile,
- *      each plane read once (grids wider than 2^24 cells run the G = 3 kernel
- *      instead; a batch launches one workgroup per work item whatever its
- *      slots_per_xcd);
+ *      each plane read once (a batch launches one workgroup per work item
+ *      whatever its slots_per_xcd);
  *   1  the sums rho, j, E are carried from each step to the next (a call
  *      first forms them from f_in) and the G groups are the waves of one
  *      workgroup;

@@ -244,7 +244,10 @@ int lbm_step(lbm_ctx* c, const double* f_in, double* f_out, int32_t nsteps, doub
     const lbm_params& p = c->p;
     const double cx = p.dt / p.dx, cy = p.dt / p.dy, ct = p.dt / p.tau;
     if (p.scheme != LBM_SCHEME_WENO5) {
-        // comparison schemes: one cell-parallel kernel per step
+        // comparison schemes: one whole-tile kernel per step
+        const int64_t tx = ((int64_t)p.nx + 63) / 64;
+        const int R = lbmi_tile_rows(tx * p.ny, tx * ((p.ny + 1) / 2));
+        const int nparts = (int)(tx * ((p.ny + R - 1) / R));
         for (int s = 0; s < nsteps; ++s) {
             const double* src = s == 0 ? f_in : (((nsteps - s) % 2 == 0) ? f_out : c->scratch);
             double* dst = ((nsteps - 1 - s) % 2 == 0) ? f_out : c->scratch;
@@ -252,9 +255,8 @@ int lbm_step(lbm_ctx* c, const double* f_in, double* f_out, int32_t nsteps, doub
             if (c->gb[0] || c->gb[1] || c->gb[2] || c->gb[3])
                 e = launch_outflow(src, p.nx, p.ny, c->gb, c->k, st);
             if (e != hipSuccess) return hip_fail(e, "lbm_step outflow");
-            int nparts = 0;
-            e = launch_step_lo(p.scheme, src, dst, c->k, ke_log ? ke_row(c, s) : nullptr, &nparts,
-                               p.nx, p.ny, p.bc, cx, cy, ct, p.ke_axis, c->gb, st);
+            e = launch_step_lo(p.scheme, R, src, dst, c->k, ke_log ? ke_row(c, s) : nullptr, p.nx,
+                               p.ny, p.bc, cx, cy, ct, p.ke_axis, c->gb, st);
             if (e != hipSuccess) return hip_fail(e, "lbm_step");
             if (ke_log && (e = reduce_ke_rows(c, s, nsteps, nparts, ke_log, st)) != hipSuccess)
                 return hip_fail(e, "lbm_step ke");
@@ -443,13 +445,18 @@ int lbm_get_step_variant(lbm_ctx* c, int32_t* v)
 //    (1024^2: 97 against 102; 2048^2: 320 against 390; the 64-instance sweep
 //    of 20768 tiles: 480 against 565), unless the last round is nearly empty
 //    (1448^2, 4.07 rounds: 231 against 210; 1101 x 605, 1.3: 102 against 67).
+int lbmi_tile_rows(int64_t t1, int64_t t2)
+{
+    constexpr int64_t RESIDENT = 512;
+    return t1 <= RESIDENT ? 1 : t2 <= RESIDENT ? 2 : 4;
+}
+
 int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4)
 {
-    constexpr int64_t RESIDENT = 512, ROUND = 2048;
+    constexpr int64_t ROUND = 2048;
     const int64_t rounds = (t4 + ROUND - 1) / ROUND;
     const bool fast = t4 >= 2 * ROUND && 100 * t4 >= 84 * ROUND * rounds;
-    const int R = t1 <= RESIDENT ? 1 : t2 <= RESIDENT ? 2 : 4;
-    const int tile_v[6] = {R, 18, 6, 1, 0, 0}, fast_v[6] = {4, 1, 2, 1, 1, 3};
+    const int tile_v[6] = {lbmi_tile_rows(t1, t2), 18, 6, 1, 0, 0}, fast_v[6] = {4, 1, 2, 1, 1, 3};
     const int* want = fast ? fast_v : tile_v;
     for (int v = 0; v < step_variant_count(); ++v) {
         int d[6];

@@ -159,10 +159,7 @@ void k_step_batch_tile(BatchArgs a, TileConsts k)
     const int ty = it.y / d->tiles_x, tx = it.y - ty * d->tiles_x;
     const TileOfBatch g{a, d, tx * TX, ty * R,
                         a.ke_part ? a.ke_part + 2 * ((int64_t)d->ke_off + it.y) : nullptr};
-    if (fast_tile(g.bc(), g.x0, g.y0, TX, R, HALO))
-        tile_step<R, NT, true>(g, k, lds);
-    else
-        tile_step<R, NT, false>(g, k, lds);
+    tile_any<R, NT, 0>(g, k, lds);
 }
 
 // Per-instance reduction of the tile partials: block i writes
@@ -341,19 +338,10 @@ void drop_graphs(lbm_batch* b)
     b->graphs.clear();
 }
 
-// The kernel of the current variant (its stand-in if an instance is wider than
-// that kernel takes).
-const BatchVariant& batch_kernel(const lbm_batch* b)
-{
-    int nx = 0;
-    for (const BatchInst& d : b->hinst) nx = std::max(nx, d.nx);
-    return kBatchVariants[step_variant_for(b->variant, nx)];
-}
-
 // Tile counts, descriptor table and work list for the current variant.
 int build_tables(lbm_batch* b)
 {
-    const BatchVariant& V = batch_kernel(b);
+    const BatchVariant& V = kBatchVariants[b->variant];
     const int per_tile = V.items();
     int64_t nwork = 0, ntiles = 0, nblk = 0;
     for (int i = 0; i < b->n; ++i) {
@@ -391,7 +379,7 @@ hipError_t launch_batch_step(lbm_batch* b, const double* src, double* dst, bool 
                              hipStream_t st, int row = 0)
 {
     double* part = b->ke_part + 2 * (int64_t)b->ke_cap * row;
-    const BatchVariant& V = batch_kernel(b);
+    const BatchVariant& V = kBatchVariants[b->variant];
     // outflow ghosts of the state this step starts from, all instances at
     // once (with a state pass, that pass writes them)
     if (b->noflow > 0 && V.M != PH_STATE) {

@@ -84,51 +84,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W))) void k_
                                  a.m_in, a.m_out, a.own_sums != 0);
 }
 
-// The whole-tile variants (lbm_tile.h): one workgroup per tile, XCD-major
-// over the strip walk as in k_step.
-struct TileArgs {
-    StepGrid s;
-    double* __restrict__ ke_part;  // [ntiles][2] or null
-    int tiles_y, nwork, per_xcd;
-    TileConsts k;
-};
-
-// One tile of the grid, as tile_step sees it.
-struct TileOfGrid {
-    const TileArgs& a;
-    int x0, y0;
-    double* ke;
-    __device__ int nx() const { return a.s.nx; }
-    __device__ int ny() const { return a.s.ny; }
-    __device__ const double* fin() const { return a.s.fin; }
-    __device__ double* fout() const { return a.s.fout; }
-    __device__ double cx() const { return a.s.cx; }
-    __device__ double cy() const { return a.s.cy; }
-    __device__ double ct() const { return a.s.ct; }
-    __device__ int ke_axis() const { return a.s.ke_axis; }
-    __device__ GridBC bc() const { return grid_bc(a.s); }
-    __device__ double side_eq(const TileConsts& k, int side, int i) const
-    {
-        return k.side_eq[side][i];
-    }
-};
-
+// The whole-tile variants (lbm_tile.h).
 template <int R, bool NT>
 __global__ __launch_bounds__((64 * TILE_WAVES)) __attribute__((amdgpu_waves_per_eu(6)))
 void k_step_tile(TileArgs a)
 {
     __shared__ double lds[TileWg<R>::LDS];
-
-    const int b = blockIdx.x;
-    const int work = (b & 7) * a.per_xcd + (b >> 3);
-    if (work >= a.nwork) return;
-    const int tile = strip_walk(work, a.s.tiles_x, a.tiles_y);
-    const int ty = tile / a.s.tiles_x, tx = tile - ty * a.s.tiles_x;
-    const TileOfGrid g{a, tx * TX, ty * R, a.ke_part ? a.ke_part + 2 * tile : nullptr};
-    if (fast_tile(g.bc(), g.x0, g.y0, TX, R, HALO))
-        tile_step<R, NT, true>(g, a.k, lds);
-    else
-        tile_step<R, NT, false>(g, a.k, lds);
+    tile_block<R, NT, 0>(a, lds);
 }
 
 // Moment sums of the cells of the band tiles around a FastRect (work item w
@@ -430,21 +392,9 @@ int step_variant_desc(int v, int info[6])
     return 0;
 }
 
-int step_variant_for(int variant, int nx)
-{
-    const StepVariant& V = kStepVariants[variant];
-    if (V.M != PH_TILE || nx <= TILE_MAX_NX) return variant;
-    // three groups of six velocities, each forming the tile's moments itself
-    for (int v = 0; v < kNumStepVariants; ++v)
-        if (kStepVariants[v].M == PH_SUMS && kStepVariants[v].G == 3 &&
-            kStepVariants[v].R == (V.R == 4 ? 4 : 2))
-            return v;
-    return 0;
-}
-
 int step_ntiles(int variant, int nx, int ny)
 {
-    const StepVariant& V = kStepVariants[step_variant_for(variant, nx)];
+    const StepVariant& V = kStepVariants[variant];
     return ((nx + TX - 1) / TX) * ((ny + V.R - 1) / V.R);
 }
 
@@ -453,7 +403,7 @@ hipError_t launch_step(int variant, const double* fin, double* fout, const Const
                        double ct, int ke_axis, const double* const gb[4], const double* m_in,
                        double* m_out, hipStream_t st, bool own_sums)
 {
-    const StepVariant& V = kStepVariants[step_variant_for(variant, nx)];
+    const StepVariant& V = kStepVariants[variant];
     if (own_sums && V.M != PH_FAST) {
         // only the fast-tile kernel forms sums in its tiles: the sums pass
         hipError_t e = launch_sums(fin, const_cast<double*>(m_in), k, (int64_t)nx * ny, st);
@@ -504,13 +454,7 @@ hipError_t launch_step(int variant, const double* fin, double* fout, const Const
         return hipGetLastError();
     }
     if (V.M == PH_TILE) {
-        TileArgs t;
-        t.s = a.s;
-        t.ke_part = ke_part;
-        t.tiles_y = a.tiles_y;
-        t.nwork = a.s.tiles_x * a.tiles_y;
-        t.per_xcd = (t.nwork + 7) / 8;
-        t.k = tile_consts(k);
+        const TileArgs t = tile_args(a.s, k, ke_part, V.R);
         hipLaunchKernelGGL(V.tile, dim3(8 * t.per_xcd), dim3(64 * TILE_WAVES), 0, st, t);
         return hipGetLastError();
     }

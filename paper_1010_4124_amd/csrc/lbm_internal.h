@@ -29,15 +29,13 @@ int lbmi_validate(const lbm_params* p);
 void lbmi_fill_consts(const lbm_params* p, lbmd::Consts* h);
 int lbmi_default_variant(int nx, int ny);
 int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4);
+int lbmi_tile_rows(int64_t t1, int64_t t2);  // rows of a whole-tile step's tiles
 int lbmi_default_adj_variant(int64_t cells);
 void lbmi_set_error(const char* msg);
 
 namespace lbmd {
 int step_variant_count();
 int step_variant_desc(int v, int info[6]);
-// the variant that a step of a grid nx cells wide launches: `variant`, or its
-// stand-in where that kernel does not take grids so wide
-int step_variant_for(int variant, int nx);
 int step_ntiles(int variant, int nx, int ny);
 hipError_t launch_step(int variant, const double* fin, double* fout, const Consts& k,
                        double* ke_part, int nx, int ny, const int bc[4], double cx, double cy,
@@ -46,9 +44,10 @@ hipError_t launch_step(int variant, const double* fin, double* fout, const Const
 // own_sums (carried-sum variants): m_in is to receive the moment sums of fin
 // (launch_sums' layout) before the step reads them; the fast-tile kernel
 // forms them in its tiles and writes only those of the band tiles to m_in
-hipError_t launch_step_lo(int scheme, const double* fin, double* fout, const Consts& k,
-                          double* ke_part, int* nparts, int nx, int ny, const int bc[4],
-                          double cx, double cy, double ct, int ke_axis,
+// one step of an upwind scheme in tiles of 64 x R cells (R = 1, 2 or 4), energy
+// partials per tile
+hipError_t launch_step_lo(int scheme, int R, const double* fin, double* fout, const Consts& k,
+                          double* ke_part, int nx, int ny, const int bc[4], double cx, double cy, double ct, int ke_axis,
                           const double* const gb[4], hipStream_t st);
 hipError_t launch_outflow(const double* f, int nx, int ny, double* const g[4], const Consts& k,
                           hipStream_t st);

@@ -95,10 +95,11 @@ struct TileWg {
 
 // A plane's rows through raw buffer accesses: the row goes in the scalar
 // offset (always inside the descriptor's range), the lane's column in the
-// vector offset, and a lane or row that must not be touched gets a vector
-// offset beyond the range (such a read gives 0, such a write is dropped).
-// Offsets stay below 2^31: the descriptors cover the few rows of a tile, and
-// step_variant_for gives wider grids than TILE_MAX_NX another kernel.
+// vector offset, and a lane that must not touch memory gets a vector offset
+// beyond the range (such a read gives 0, such a write is dropped). Fast tiles
+// have one descriptor per plane, over the tile's rows, whose offsets stay below
+// 2^31 on grids up to TILE_MAX_NX cells wide; boundary tiles, and every tile of
+// a wider grid, one per row, over the tile's columns.
 constexpr int TILE_MAX_NX = 1 << 24;
 constexpr unsigned TILE_SKIP = 0x80000000u;
 
@@ -184,7 +185,7 @@ __device__ __forceinline__ void tile_load(const Grid& g, const TileConsts& k, co
     const int64_t plane = (int64_t)nx * ny;
     const double* fin = g.fin();
     const int w = FAST ? 64 : min(64, nx - x0);
-    const unsigned vx8 = FAST || lane < w ? 8u * (unsigned)(x0 + lane) : TILE_SKIP;
+    const unsigned l8 = 8u * (unsigned)lane, vx8 = l8 + 8u * (unsigned)x0;  // (vx8: fast tiles)
     const bool hl = lane < 5 * R;
     const int hr = lane / 5, hq = lane - 5 * hr;
     const int yhx = x0 + halo_col(hq, v.ynegx, w), nhx = x0 + halo_col(hq, v.nnegx, w);
@@ -219,7 +220,7 @@ __device__ __forceinline__ void tile_load(const Grid& g, const TileConsts& k, co
             if (rd.mode == RM_OUT)
                 src = (rd.side == YLO ? b.gb[YLO] : b.gb[YHI]) + (int64_t)v.iy * nx;
             const bool ld = rd.mode != RM_CONST && rd.mode != RM_NONE;
-            L.p[j] = row_load(rows_rsrc(src, ld ? rb : 0), vx8, 0);
+            L.p[j] = row_load(rows_rsrc(src + x0, ld ? 8 * w : 0), l8, 0);
         }
         // halo values of the rows inside the domain
         auto halo = [&](int i, int imx, int hx, int hy) {
@@ -239,7 +240,8 @@ __device__ __forceinline__ void tile_load(const Grid& g, const TileConsts& k, co
 #pragma unroll
             for (int j = 0; j < R; ++j)
                 L.pn[j] = row_load(
-                    rows_rsrc(fin + v.in * plane + (int64_t)min(y0 + j, ny - 1) * nx, rb), vx8, 0);
+                    rows_rsrc(fin + v.in * plane + (int64_t)min(y0 + j, ny - 1) * nx + x0, 8 * w),
+                    l8, 0);
             L.hn = halo(v.in, 1 + 6 * v.sn + (v.nnegx ? 5 : 2), nhx, y0 + hr);
         }
         // rows of a fixed-equilibrium side
@@ -250,14 +252,38 @@ __device__ __forceinline__ void tile_load(const Grid& g, const TileConsts& k, co
         }
     }
     if (hasm)
-        L.f0 = row_load(rows_rsrc(fin + (int64_t)y0 * nx, R * rb),
-                        FAST || y0 + v.m < ny ? vx8 : TILE_SKIP, uniform(v.m * rb));
+        L.f0 = row_load(rows_rsrc(fin + (int64_t)(y0 + v.m) * nx + x0,
+                                  FAST || y0 + v.m < ny ? 8 * w : 0), l8, 0);
+}
+
+// Flux differences of f along a strip of R cells from its upwind-ordered
+// samples P (P[m+3] is cell m): WENO5, or the upwind schemes, whose face
+// downstream of a cell c with upstream neighbour b takes c (first order) or
+// c + (c - b) / 2 (second order).
+template <int R, int SCHEME>
+__device__ __forceinline__ void strip_diff(const double (&P)[R + 5], double eps, double (&dh)[R])
+{
+    if constexpr (SCHEME == 0) {
+        weno_strip<R, false>(P, eps, [&](int m, double d) { dh[m] = d; });
+    } else {
+        auto face = [&](int j) {
+            return SCHEME == 1 ? P[j + 2] : __builtin_fma(0.5, P[j + 2] - P[j + 1], P[j + 2]);
+        };
+        double hp = face(0);
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            const double h = face(m + 1);
+            dh[m] = h - hp;
+            hp = h;
+        }
+    }
 }
 
 // Tile g (FAST: a fast tile) by one workgroup. g is a Grid (the accessors used
 // below) with the tile's origin x0, y0 and its energy partial ke (null: none
 // wanted). lds holds TileWg<R>::LDS doubles.
-template <int R, bool NT, bool FAST, class Grid>
+// SCHEME: the convection flux (lbm_params.scheme).
+template <int R, bool NT, bool FAST, int SCHEME, class Grid>
 __device__ __forceinline__ void tile_step(const Grid& g, const TileConsts& k, double* lds)
 {
     using S = TileWg<R>;
@@ -341,8 +367,8 @@ __device__ __forceinline__ void tile_step(const Grid& g, const TileConsts& k, do
         const double F0 = 1.0 - 6.0 * (F1 + F2 + F3);
         const double fe = c.rho * F0 * c.t0;
         row_store<false>(__builtin_fma(-ct, f0 - fe, f0),
-                         rows_rsrc(g.fout() + (int64_t)y0 * nx, R * rb),
-                         act ? 8u * (unsigned)(g.x0 + lane) : TILE_SKIP, uniform(m * rb));
+                         rows_rsrc(g.fout() + (int64_t)(y0 + m) * nx + g.x0,
+                                   FAST || y0 + m < ny ? 8 * wd : 0), 8u * (unsigned)lane, 0);
         if (g.ke) {
             const double un = (g.ke_axis() ? jx : jy) / r;
             const double e = act ? 0.5 * r * un * un : 0.0;
@@ -369,10 +395,10 @@ __device__ __forceinline__ void tile_step(const Grid& g, const TileConsts& k, do
         const double* b = s_pl + xr * PITCH + xs * R;
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) P[j] = b[j];
-        weno_strip<R, false>(P, eps, [&](int q, double dd) { dh[q] = dd; });
+        strip_diff<R, SCHEME>(P, eps, dh);
         pin(dh);
     };
-    weno_strip<R, false>(L.p, ky.ey, [&](int q, double dd) { dhy[q] = dd; });
+    strip_diff<R, SCHEME>(L.p, ky.ey, dhy);
     pin(dhy);
     x_strip(s_y, ky.eh, dhx);
     if (v.hasn) x_strip(s_n, kn.ek, dhn);
@@ -408,12 +434,18 @@ __device__ __forceinline__ void tile_step(const Grid& g, const TileConsts& k, do
     }
     plane_sync<2>();
     const double omct = 1.0 - g.ct();
-    const unsigned vx8 = FAST || lane < wd ? 8u * (unsigned)(g.x0 + lane) : TILE_SKIP;
+    // f' of plane i in the lane's column of row m of the tile
+    auto put = [&](int i, int m, double x) {
+        double* row = g.fout() + i * plane + (int64_t)y0 * nx + g.x0;
+        if constexpr (FAST)
+            row_store<NT>(x, rows_rsrc(row, R * rb), 8u * (unsigned)lane, uniform(m * rb));
+        else
+            row_store<NT>(x, rows_rsrc(row + (int64_t)m * nx, y0 + m < ny ? 8 * wd : 0),
+                          8u * (unsigned)lane, 0);
+    };
     {
         const double vx = v.ynegx ? -ky.vh : ky.vh, vy = v.negy ? -ky.vs : ky.vs;
         const double ncx = -(g.cx() * ky.vh), ncy = -(g.cy() * ky.vs);
-        const __amdgpu_buffer_rsrc_t ro =
-            rows_rsrc(g.fout() + v.iy * plane + (int64_t)y0 * nx, R * rb);
 #pragma unroll
         for (int mc = 0; mc < R; ++mc) {
             const int mr = v.negy ? R - 1 - mc : mc;
@@ -423,13 +455,11 @@ __device__ __forceinline__ void tile_step(const Grid& g, const TileConsts& k, do
                                       sc[v.sy * R * 64] * feq_poly(eta, sc[5 * R * 64]));
             fn = __builtin_fma(ncx, s_y[mc * XPITCH + ylc], fn);
             fn = __builtin_fma(ncy, dhy[mc], fn);
-            row_store<NT>(fn, ro, FAST || y0 + mr < ny ? vx8 : TILE_SKIP, uniform(mr * rb));
+            put(v.iy, mr, fn);
         }
     }
     if (v.hasn) {
         const double vx = v.nnegx ? -kn.vk : kn.vk, ncx = -(g.cx() * kn.vk);
-        const __amdgpu_buffer_rsrc_t ro =
-            rows_rsrc(g.fout() + v.in * plane + (int64_t)y0 * nx, R * rb);
 #pragma unroll
         for (int mc = 0; mc < R; ++mc) {
             const double* sc = st + mc * 64 + lane;
@@ -438,9 +468,74 @@ __device__ __forceinline__ void tile_step(const Grid& g, const TileConsts& k, do
             double fn = __builtin_fma(omct, fn_[mc],
                                       sc[v.sn * R * 64] * feq_poly(eta, sc[5 * R * 64]));
             fn = __builtin_fma(ncx, s_n[mc * XPITCH + nlc], fn);
-            row_store<NT>(fn, ro, FAST || y0 + mc < ny ? vx8 : TILE_SKIP, uniform(mc * rb));
+            put(v.in, mc, fn);
         }
     }
+}
+
+// Tile g of either kind.
+template <int R, bool NT, int SCHEME, class Grid>
+__device__ __forceinline__ void tile_any(const Grid& g, const TileConsts& k, double* lds)
+{
+    if (g.nx() <= TILE_MAX_NX && fast_tile(g.bc(), g.x0, g.y0, TX, R, HALO))
+        tile_step<R, NT, true, SCHEME>(g, k, lds);
+    else
+        tile_step<R, NT, false, SCHEME>(g, k, lds);
+}
+
+// A launch over one grid: one workgroup per tile, XCD-major over the strip walk
+// as in k_step.
+struct TileArgs {
+    StepGrid s;
+    double* __restrict__ ke_part;  // [ntiles][2] or null
+    int tiles_y, nwork, per_xcd;
+    TileConsts k;
+};
+
+// One tile of the grid, as tile_step sees it.
+struct TileOfGrid {
+    const TileArgs& a;
+    int x0, y0;
+    double* ke;
+    __device__ int nx() const { return a.s.nx; }
+    __device__ int ny() const { return a.s.ny; }
+    __device__ const double* fin() const { return a.s.fin; }
+    __device__ double* fout() const { return a.s.fout; }
+    __device__ double cx() const { return a.s.cx; }
+    __device__ double cy() const { return a.s.cy; }
+    __device__ double ct() const { return a.s.ct; }
+    __device__ int ke_axis() const { return a.s.ke_axis; }
+    __device__ GridBC bc() const { return grid_bc(a.s); }
+    __device__ double side_eq(const TileConsts& k, int side, int i) const
+    {
+        return k.side_eq[side][i];
+    }
+};
+
+inline TileArgs tile_args(const StepGrid& s, const Consts& k, double* ke_part, int R)
+{
+    TileArgs t;
+    t.s = s;
+    t.s.tiles_x = (s.nx + TX - 1) / TX;
+    t.ke_part = ke_part;
+    t.tiles_y = (s.ny + R - 1) / R;
+    t.nwork = t.s.tiles_x * t.tiles_y;
+    t.per_xcd = (t.nwork + 7) / 8;
+    t.k = tile_consts(k);
+    return t;
+}
+
+// Workgroup blockIdx.x of such a launch.
+template <int R, bool NT, int SCHEME>
+__device__ __forceinline__ void tile_block(const TileArgs& a, double* lds)
+{
+    const int b = blockIdx.x;
+    const int work = (b & 7) * a.per_xcd + (b >> 3);
+    if (work >= a.nwork) return;
+    const int tile = strip_walk(work, a.s.tiles_x, a.tiles_y);
+    const int ty = tile / a.s.tiles_x, tx = tile - ty * a.s.tiles_x;
+    tile_any<R, NT, SCHEME>(
+        TileOfGrid{a, tx * TX, ty * R, a.ke_part ? a.ke_part + 2 * tile : nullptr}, a.k, lds);
 }
 
 }  // namespace lbmd

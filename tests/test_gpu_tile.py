@@ -3,9 +3,11 @@ sizes where their tiles begin and end, against the (4, 1, 2, 1, 0, 1) variant,
 which the oracle tests cover: the same expressions in the same order, so the
 populations are equal bit for bit; the energy logs add the same terms in
 another order (n terms: relative difference below n 2^-53)."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_1010_4124_amd import inputs, lbm
 
 pytestmark = pytest.mark.gpu
@@ -71,9 +73,8 @@ def test_default_variant_and_batches_of_it():
                 assert torch.equal(b.view(out, i), c.step(b.view(f0, i).contiguous(), 5)), (v, i)
 
 
-def test_very_wide_grid_takes_the_stand_in():
-    """Grids wider than the whole-tile kernel addresses run the kernel that
-    stands in for it: the same step to rounding (1e-13 of the largest value)."""
+def test_very_wide_grid():
+    """Past 2^24 cells per row, where every tile takes the boundary path."""
     tile, ref = _variants()
     nx = (1 << 24) + 5
     ctx = lbm.Context(nx, 1, 2e-2, 2e-2, 4e-4, 6e-4, (P, P, P, P))
@@ -86,4 +87,22 @@ def test_very_wide_grid_takes_the_stand_in():
     for v in tile:
         ctx.variant = v
         ctx.step(f, out=out)
-        assert float((out - want).abs().max()) <= 1e-13 * float(want.abs().max())
+        assert torch.equal(out, want), v
+
+
+@pytest.mark.parametrize("shape", [(201, 203), (301, 305)])
+@pytest.mark.parametrize("scheme", [lbm.UPWIND1, lbm.UPWIND2])
+def test_upwind_schemes_on_grids_of_higher_tiles(shape, scheme):
+    """Grids whose upwind step takes tiles of 2 and of 4 rows, against the
+    oracle (normwise 1e-12, the bar of the schemes' other cases)."""
+    nx, ny = shape
+    bc = (R, O, P, P)
+    f = inputs.random_f(nx, ny, seed=9)
+    p = oracle.OracleParams.make(nx, ny, 2e-2, 2.5e-2, 4e-4, 6e-4, bc, side_state=SIDES,
+                                 scheme=scheme)
+    want = oracle.step(p, f, 3, nthreads=8)
+    ctx = lbm.Context(nx, ny, 2e-2, 2.5e-2, 4e-4, 6e-4, bc, side_state=SIDES, scheme=scheme)
+    got, ke = ctx.step(torch.from_numpy(f).cuda(), 3, ke_log=True)
+    assert np.abs(got.cpu().numpy() - want).max() <= 1e-12 * np.abs(want).max()
+    e = oracle.kinetic_y(p, f)
+    assert ke[0].cpu().numpy() == pytest.approx(np.asarray(e), rel=1e-12)
