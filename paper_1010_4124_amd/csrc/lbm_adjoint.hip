@@ -131,31 +131,37 @@ __device__ __forceinline__ void weno_face_bar_g(const double (&g)[4], const doub
     Gg[3] = __builtin_fma(-0.125, R3, D2b);
 }
 
-// Gather of one line strip: fw[0..R+7] are f at strip positions -4..R+3,
-// lw[0..R+5] are lambda' at positions -3..R+2; returns in acc[m] the sum over
-// the faces touching strip cell m of mu dh/df(m) (including the factor v).
+// Faces of one line strip of R cells: fw[0..R+7] are f at the strip's upwind-
+// ordered positions -4..R+3, lw[0..R+5] lambda' at positions -3..R+2, cn the
+// Courant factor dt / spacing with the sign of v. Adds to Gp[0..R+7] what the
+// R+4 faces that touch the strip's cells give the samples F = v f (mu dh/dF).
 // The faces' first and second differences and E terms slide along the strip
-// as in the forward weno_faces.
-template <int R, bool NEG>
-__device__ __forceinline__ void gather_strip(const double (&fw)[R + 8], const double (&lw)[R + 6],
-                                             double v, double cn, double eps, double (&acc)[R])
+// as in the forward weno_faces. SEQ: one face after the other, for fewer
+// registers.
+template <int R, bool SEQ = false>
+__device__ __forceinline__ void gather_faces(const double (&fw)[R + 8], const double (&lw)[R + 6],
+                                             double v, double cn, double eps, double (&Gp)[R + 8])
 {
     constexpr double C13 = 13.0 / 12.0;
-    double Pw[R + 8];
+    double Pl = v * fw[4];
+    double g[4], D[3], E[3];
+    {
+        const double P0 = v * fw[0], P1 = v * fw[1], P2 = v * fw[2], P3 = v * fw[3];
+        g[0] = P1 - P0;
+        g[1] = P2 - P1;
+        g[2] = P3 - P2;
+        g[3] = Pl - P3;
+    }
 #pragma unroll
-    for (int q = 0; q < R + 8; ++q) Pw[q] = v * (NEG ? fw[R + 7 - q] : fw[q]);
-    // dL/dP at the R+8 upwind-ordered positions
-    double Gp[R + 8];
-#pragma unroll
-    for (int q = 0; q < R + 8; ++q) Gp[q] = 0.0;
-    double g[4] = {Pw[1] - Pw[0], Pw[2] - Pw[1], Pw[3] - Pw[2], Pw[4] - Pw[3]};
-    double D[3] = {g[1] - g[0], g[2] - g[1], g[3] - g[2]};
-    double E[3] = {__builtin_fma(C13 * D[0], D[0], eps), __builtin_fma(C13 * D[1], D[1], eps),
-                   __builtin_fma(C13 * D[2], D[2], eps)};
+    for (int q = 0; q < 3; ++q) {
+        D[q] = g[q + 1] - g[q];
+        E[q] = __builtin_fma(C13 * D[q], D[q], eps);
+    }
 #pragma unroll
     for (int t = 0; t < R + 4; ++t) {
-        // face between strip positions I and I+1: I = t-2 (v >= 0) or R-t (v < 0)
-        const double mu = NEG ? cn * (lw[R + 4 - t] - lw[R + 3 - t]) : cn * (lw[t + 2] - lw[t + 1]);
+        if (SEQ) __builtin_amdgcn_sched_barrier(0);
+        // face between positions t-2 and t-1
+        const double mu = cn * (lw[t + 2] - lw[t + 1]);
         double Gg[4];
         const double CD[3] = {C13 * D[0], C13 * D[1], C13 * D[2]};
         weno_face_bar_g(g, D, CD, E, mu, Gg);
@@ -166,10 +172,12 @@ __device__ __forceinline__ void gather_strip(const double (&fw)[R + 8], const do
         Gp[t + 3] += Gg[2] - Gg[3];
         Gp[t + 4] += Gg[3];
         if (t + 1 < R + 4) {
+            const double Pn = v * fw[t + 5];
             g[0] = g[1];
             g[1] = g[2];
             g[2] = g[3];
-            g[3] = Pw[t + 5] - Pw[t + 4];
+            g[3] = Pn - Pl;
+            Pl = Pn;
             D[0] = D[1];
             D[1] = D[2];
             D[2] = g[3] - g[2];
@@ -178,6 +186,24 @@ __device__ __forceinline__ void gather_strip(const double (&fw)[R + 8], const do
             E[2] = __builtin_fma(C13 * D[2], D[2], eps);
         }
     }
+}
+
+// Gather of one line strip given in natural order (NEG: v < 0, the strip is
+// walked from its other end): returns in acc[m] the sum over the faces touching
+// strip cell m of mu dh/df(m) (including the factor v).
+template <int R, bool NEG>
+__device__ __forceinline__ void gather_strip(const double (&fw)[R + 8], const double (&lw)[R + 6],
+                                             double v, double cn, double eps, double (&acc)[R])
+{
+    double fc[R + 8], lc[R + 6], Gp[R + 8];
+#pragma unroll
+    for (int q = 0; q < R + 8; ++q) {
+        fc[q] = NEG ? fw[R + 7 - q] : fw[q];
+        Gp[q] = 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < R + 6; ++q) lc[q] = NEG ? lw[R + 5 - q] : lw[q];
+    gather_faces<R>(fc, lc, v, NEG ? -cn : cn, eps, Gp);
 #pragma unroll
     for (int m = 0; m < R; ++m) acc[m] = v * Gp[NEG ? R + 3 - m : m + 4];
 }
@@ -472,25 +498,71 @@ struct AdjCell {
     double K0, Kx, Ky, KE, rest;  // rest: the rest particle's adjoint
 };
 
-// The cell's terms from its moment sums r = sum f, (jx, jy) = sum f v,
-// E = sum f |v|^2 / 2 (Eq. (10)) and lambda'.
+// A cell's state from its moment sums r = sum f, (jx, jy) = sum f v, E = sum f
+// |v|^2 / 2 (Eq. (10)), and the sums over the velocities of lambda'_i times the
+// partials of f_i^eq (Eq. (28)), P = (1-b)(1+eta) + eta^2/2 + eta^3/6,
+// eta = v.u / T.
+struct AdjSums {
+    double r, E, ux, uy, T, iT, t0, b;
+    double sP = 0.0, sX = 0.0, sY = 0.0, sT = 0.0;
+
+    __device__ __forceinline__ AdjSums(double r_, double jx, double jy, double E_) : r(r_), E(E_)
+    {
+        ux = jx / r;
+        uy = jy / r;
+        const double u2 = ux * ux + uy * uy;
+        T = E / r - 0.5 * u2;
+        iT = 1.0 / T;
+        t0 = 1.0 - u2 / (2.0 * T);
+        b = 1.0 - t0;
+    }
+    // velocity (vx, vy): its lambda', the weight of its shell and its T derivative
+    __device__ __forceinline__ void add(double L, double vx, double vy, double Fs, double dFs)
+    {
+        const double eta = __builtin_fma(vx, ux * iT, vy * (uy * iT));
+        const double P = feq_poly(eta, t0);
+        const double Pxi = t0 + eta * (1.0 + 0.5 * eta);        // T dP/dxi
+        const double Pb = -(1.0 + eta);                          // dP/db
+        const double PTT = -eta * (t0 + eta * (1.0 + 0.5 * eta));  // T dP/dT at fixed xi, b
+        const double LF = L * Fs;
+        sP = __builtin_fma(LF, P, sP);
+        sX = __builtin_fma(LF, __builtin_fma(Pxi, vx, Pb * ux), sX);
+        sY = __builtin_fma(LF, __builtin_fma(Pxi, vy, Pb * uy), sY);
+        sT += L * __builtin_fma(dFs * T, P, Fs * (PTT - Pb * b));
+    }
+    // f^eq depends on (rho, ux, uy, T): d/drho = F P, d/du = rho F (Pxi v + Pb u)/T,
+    // d/dT = rho (F' P + F (PTT - Pb b) / T); l0: lambda' of the rest particle
+    __device__ __forceinline__ AdjCell finish(double l0, double ct, double wdxdy) const
+    {
+        double rb = sP, uxb = r * iT * sX, uyb = r * iT * sY, Tb = r * iT * sT;
+        // T = E/rho - u^2/2, u = j/rho
+        const double Eb = Tb / r;
+        rb -= Tb * (E / (r * r));
+        const double uxb2 = uxb - Tb * ux, uyb2 = uyb - Tb * uy;
+        const double jxb = uxb2 / r, jyb = uyb2 / r;
+        rb -= (uxb2 * ux + uyb2 * uy) / r;
+        AdjCell c;
+        c.K0 = __builtin_fma(ct, rb, -0.5 * wdxdy * uy * uy);
+        c.Kx = ct * jxb;
+        c.Ky = __builtin_fma(ct, jyb, wdxdy * uy);
+        c.KE = ct * Eb;
+        // rest particle: no convection
+        c.rest = __builtin_fma(1.0 - ct, l0, c.K0);
+        return c;
+    }
+};
+
+// The cell's terms from its moment sums and lambda'.
 template <class LV>
 __device__ __forceinline__ AdjCell adj_cell_sums(double r, double jx, double jy, double E, LV&& lv,
                                                  const Consts& k, double ct, double wdxdy)
 {
-    const double ux = jx / r, uy = jy / r;
-    const double u2 = ux * ux + uy * uy;
-    const double T = E / r - 0.5 * u2;
-    const double iT = 1.0 / T;
-    const double t0 = 1.0 - u2 / (2.0 * T);
-    const double b = 1.0 - t0;
-    const double F1 = weight_c(k, 0, T), F2 = weight_c(k, 1, T), F3 = weight_c(k, 2, T);
+    AdjSums c(r, jx, jy, E);
+    const double F1 = weight_c(k, 0, c.T), F2 = weight_c(k, 1, c.T), F3 = weight_c(k, 2, c.T);
     const double F0 = 1.0 - 6.0 * (F1 + F2 + F3);
-    const double d1 = dweight_c(k, 0, T), d2 = dweight_c(k, 1, T), d3 = dweight_c(k, 2, T);
+    const double d1 = dweight_c(k, 0, c.T), d2 = dweight_c(k, 1, c.T), d3 = dweight_c(k, 2, c.T);
     const double d0 = -6.0 * (d1 + d2 + d3);
-    // sums over i of lambda'_i times the partials of f_i^eq (Eq. (28)),
-    // with P = (1-b)(1+eta) + eta^2/2 + eta^3/6, eta = v.u / T
-    double sP = 0.0, sX = 0.0, sY = 0.0, sT = 0.0, l0 = 0.0;
+    double l0 = 0.0;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const double L = lv(i);
@@ -498,34 +570,9 @@ __device__ __forceinline__ AdjCell adj_cell_sums(double r, double jx, double jy,
         // weight of the speed shell of velocity i and its T derivative
         const double Fs = i == 0 ? F0 : i < 7 ? F1 : i < 13 ? F2 : F3;
         const double dFs = i == 0 ? d0 : i < 7 ? d1 : i < 13 ? d2 : d3;
-        const double eta = __builtin_fma(k.vx[i], ux * iT, k.vy[i] * (uy * iT));
-        const double P = feq_poly(eta, t0);
-        const double Pxi = t0 + eta * (1.0 + 0.5 * eta);        // T dP/dxi
-        const double Pb = -(1.0 + eta);                          // dP/db
-        const double PTT = -eta * (t0 + eta * (1.0 + 0.5 * eta));  // T dP/dT at fixed xi, b
-        const double LF = L * Fs;
-        sP = __builtin_fma(LF, P, sP);
-        sX = __builtin_fma(LF, __builtin_fma(Pxi, k.vx[i], Pb * ux), sX);
-        sY = __builtin_fma(LF, __builtin_fma(Pxi, k.vy[i], Pb * uy), sY);
-        sT += L * __builtin_fma(dFs * T, P, Fs * (PTT - Pb * b));
+        c.add(L, k.vx[i], k.vy[i], Fs, dFs);
     }
-    // f^eq depends on (rho, ux, uy, T): d/drho = F P, d/du = rho F (Pxi v + Pb u)/T,
-    // d/dT = rho (F' P + F (PTT - Pb b) / T)
-    double rb = sP, uxb = r * iT * sX, uyb = r * iT * sY, Tb = r * iT * sT;
-    // T = E/rho - u^2/2, u = j/rho
-    const double Eb = Tb / r;
-    rb -= Tb * (E / (r * r));
-    const double uxb2 = uxb - Tb * ux, uyb2 = uyb - Tb * uy;
-    const double jxb = uxb2 / r, jyb = uyb2 / r;
-    rb -= (uxb2 * ux + uyb2 * uy) / r;
-    AdjCell c;
-    c.K0 = __builtin_fma(ct, rb, -0.5 * wdxdy * uy * uy);
-    c.Kx = ct * jxb;
-    c.Ky = __builtin_fma(ct, jyb, wdxdy * uy);
-    c.KE = ct * Eb;
-    // rest particle: no convection
-    c.rest = __builtin_fma(1.0 - ct, l0, c.K0);
-    return c;
+    return c.finish(l0, ct, wdxdy);
 }
 
 // The same from f: its sums in the order of k_sums and of the carried-sum
@@ -1175,6 +1222,12 @@ __global__ __launch_bounds__(256) void k_rowdot(const double* __restrict__ A,
     if (threadIdx.x == 0) out[m] = sr[0] + sr[1] + sr[2] + sr[3];
 }
 
+}  // namespace lbmd
+
+#include "lbm_adj_tile.h"
+
+namespace lbmd {
+
 // ---------------------------------------------------------------------------
 // Reverse-step variants: rows per lane R, velocity groups G, waves-per-SIMD
 // target W and whether a state pass forms the K's first (PS).
@@ -1195,6 +1248,7 @@ static const AdjVariant kAdjVariants[] = {
     LBM_ADJ_VARIANT(4, 6, 1, 1) LBM_ADJ_VARIANT(4, 3, 1, 1)
     LBM_ADJ_MARCH(64, 2) LBM_ADJ_MARCH(128, 2) LBM_ADJ_MARCH(256, 2) LBM_ADJ_MARCH(32, 2)
     LBM_ADJ_MARCH(16, 2)
+    {4, 18, 3, 0, k_adj_tile<4>}
 };
 #undef LBM_ADJ_VARIANT
 #undef LBM_ADJ_MARCH
@@ -1234,6 +1288,12 @@ hipError_t launch_adjoint(int variant, const double* f, const double* sums, cons
     a.ct = ct;
     a.wdxdy = wdxdy;
     a.k = k;
+    if (V.PS == 0 && V.G == 18) {  // whole-tile variants
+        a.nwork = a.tiles_x * a.tiles_y;
+        a.per_xcd = (a.nwork + 7) / 8;
+        hipLaunchKernelGGL(V.kernel, dim3(8 * a.per_xcd), dim3(64 * TILE_WAVES), 0, st, a);
+        return hipGetLastError();
+    }
     if (V.PS) {
         const int64_t n = (int64_t)nx * ny;
         if (sums)

@@ -16,6 +16,8 @@
 using namespace lbmd;
 
 namespace {
+constexpr int KE_ROWS = 32;  // steps whose energy partials one launch reduces, at most
+
 thread_local std::string g_err;
 
 // Stores the message of the calling thread's last failure; never throws (on
@@ -132,22 +134,23 @@ int lbm_create(const lbm_params* p, lbm_ctx** out)
     lbmi_fill_consts(p, &c->k);
     const size_t n = (size_t)p->nx * p->ny;
     c->variant = lbmi_default_variant(p->nx, p->ny);
-    c->adj_variant = lbmi_default_adj_variant((int64_t)p->nx * p->ny);
-    int maxtiles = 0;
+    c->adj_variant = lbmi_default_adj_variant(p->nx, p->ny);
+    // energy partials: room for one step of any variant, and for KE_ROWS steps,
+    // reduced by one launch, of those with tiles of two rows or more (fewer
+    // where that would take more than 64 MiB)
+    size_t most = (n + 255) / 256, tall = most;
     for (int v = 0; v < step_variant_count(); ++v) {
-        const int t = step_ntiles(v, p->nx, p->ny);
-        if (t > maxtiles) maxtiles = t;
+        int d[6];
+        step_variant_desc(v, d);
+        const size_t t = (size_t)step_ntiles(v, p->nx, p->ny);
+        most = std::max(most, t);
+        if (d[0] > 1) tall = std::max(tall, t);
     }
-    c->ke_cap = maxtiles > (int)((n + 255) / 256) ? maxtiles : (int)((n + 255) / 256);
+    const size_t rows = std::max<size_t>(1, std::min<size_t>(KE_ROWS, (64u << 20) / (16 * tall)));
     // the same buffer first receives the 4 x 19 fixed-side equilibria
-    if (2 * c->ke_cap < 4 * NV) c->ke_cap = 2 * NV;
-    // energy partials of up to KE_ROWS steps, reduced by one launch (fewer
-    // rows where that would take more than 64 MiB)
-    constexpr int KE_ROWS = 32;
-    const size_t row_bytes = 2 * (size_t)c->ke_cap * sizeof(double);
-    c->ke_rows = (int)std::max<size_t>(1, std::min<size_t>(KE_ROWS, (64u << 20) / row_bytes));
+    c->ke_cap = (int64_t)std::max<size_t>({rows * tall, most, 2 * NV});
     if ((e = hipMalloc(&c->scratch, NV * n * sizeof(double))) != hipSuccess ||
-        (e = hipMalloc(&c->ke_part, row_bytes * c->ke_rows)) != hipSuccess ||
+        (e = hipMalloc(&c->ke_part, 16 * (size_t)c->ke_cap)) != hipSuccess ||
         (e = hipMalloc(&c->colbuf, (size_t)p->nx * sizeof(double))) != hipSuccess ||
         (e = hipMalloc(&c->msum, 8 * n * sizeof(double))) != hipSuccess ||
         (e = hipMalloc(&c->gbuf, NV * 2 * ((size_t)p->nx + p->ny) * sizeof(double))) !=
@@ -211,10 +214,16 @@ int lbm_init(lbm_ctx* c, const double* rho, const double* ux, const double* uy, 
     return e == hipSuccess ? LBM_OK : hip_fail(e, "lbm_init");
 }
 
-// Row of the energy partials that step s of a call writes.
-static double* ke_row(lbm_ctx* c, int s)
+// Rows of nparts energy partials that the buffer holds, at most KE_ROWS.
+static int ke_rows(const lbm_ctx* c, int nparts)
 {
-    return c->ke_part + 2 * (int64_t)c->ke_cap * (s % c->ke_rows);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(KE_ROWS, c->ke_cap / nparts));
+}
+
+// Row of the energy partials that step s of a call writes.
+static double* ke_row(lbm_ctx* c, int s, int nparts)
+{
+    return c->ke_part + 2 * (int64_t)nparts * (s % ke_rows(c, nparts));
 }
 
 // After step s of nsteps: when s fills the last row or is the last step,
@@ -223,10 +232,11 @@ static double* ke_row(lbm_ctx* c, int s)
 static hipError_t reduce_ke_rows(lbm_ctx* c, int s, int nsteps, int nparts, double* ke_log,
                                  hipStream_t st)
 {
-    if ((s + 1) % c->ke_rows != 0 && s != nsteps - 1) return hipSuccess;
-    const int rows = s % c->ke_rows + 1;
-    return launch_reduce_pairs(c->ke_part, nparts, rows, 2 * (int64_t)c->ke_cap,
-                               c->p.dx * c->p.dy, ke_log + 2 * (s + 1 - rows), st);
+    const int most = ke_rows(c, nparts);
+    if ((s + 1) % most != 0 && s != nsteps - 1) return hipSuccess;
+    const int rows = s % most + 1;
+    return launch_reduce_pairs(c->ke_part, nparts, rows, 2 * (int64_t)nparts, c->p.dx * c->p.dy,
+                               ke_log + 2 * (s + 1 - rows), st);
 }
 
 int lbm_step(lbm_ctx* c, const double* f_in, double* f_out, int32_t nsteps, double* ke_log,
@@ -255,7 +265,7 @@ int lbm_step(lbm_ctx* c, const double* f_in, double* f_out, int32_t nsteps, doub
             if (c->gb[0] || c->gb[1] || c->gb[2] || c->gb[3])
                 e = launch_outflow(src, p.nx, p.ny, c->gb, c->k, st);
             if (e != hipSuccess) return hip_fail(e, "lbm_step outflow");
-            e = launch_step_lo(p.scheme, R, src, dst, c->k, ke_log ? ke_row(c, s) : nullptr, p.nx,
+            e = launch_step_lo(p.scheme, R, src, dst, c->k, ke_log ? ke_row(c, s, nparts) : nullptr, p.nx,
                                p.ny, p.bc, cx, cy, ct, p.ke_axis, c->gb, st);
             if (e != hipSuccess) return hip_fail(e, "lbm_step");
             if (ke_log && (e = reduce_ke_rows(c, s, nsteps, nparts, ke_log, st)) != hipSuccess)
@@ -263,7 +273,7 @@ int lbm_step(lbm_ctx* c, const double* f_in, double* f_out, int32_t nsteps, doub
         }
         return LBM_OK;
     }
-    const int ntiles = step_ntiles(c->variant, p.nx, p.ny);
+    const int ntiles = step_ntiles(c->variant, p.nx, p.ny), blocks = (int)((n + 255) / 256);
     int info[6];
     step_variant_desc(c->variant, info);
     const int mode = info[5];
@@ -290,12 +300,12 @@ int lbm_step(lbm_ctx* c, const double* f_in, double* f_out, int32_t nsteps, doub
         } else if (mode == 2) {
             // state pass: cell state, rest particle and energy partials
             hipError_t e = launch_state(src, dst, c->msum, p.nx, p.ny, ct, p.ke_axis,
-                                        ke_log ? ke_row(c, s) : nullptr, &nparts, c->k, c->gb, st);
+                                        ke_log ? ke_row(c, s, blocks) : nullptr, &nparts, c->k, c->gb, st);
             if (e != hipSuccess) return hip_fail(e, "lbm_step state");
             m_in = c->msum;
         }
         hipError_t e = launch_step(c->variant, src, dst, c->k,
-                                   ke_log && mode != 2 ? ke_row(c, s) : nullptr, p.nx, p.ny, p.bc,
+                                   ke_log && mode != 2 ? ke_row(c, s, nparts) : nullptr, p.nx, p.ny, p.bc,
                                    cx, cy, ct, p.ke_axis, c->gb, m_in, m_out, st,
                                    carry && s == 0);
         if (e != hipSuccess) return hip_fail(e, "lbm_step");
@@ -598,12 +608,21 @@ int lbm_tune_step(lbm_ctx* c, const double* f_in, double* f_tmp, int32_t nsteps,
     return rc;
 }
 
-// Default reverse-step variant: one velocity per workgroup after a state
-// pass, so that small grids still fill the chip; from 2^20 cells on, the
-// marching variant in chunks of 64 rows.
-int lbmi_default_adj_variant(int64_t cells)
+// Default reverse-step variant. Measured on MI355X (shear layers, us a step,
+// whole-tile kernel / marching kernel with chunks of 32 rows / of 64 rows / one
+// velocity per 64 x 4 tile after a state pass):
+//   128^2 21 / 28 / - / 27, 256^2 23 / 33 / - / 40, 600 x 200 42 / 51 / 56 / 69,
+//   384^2 55 / 51 / 58 / 61, 512^2 73 / 72 / 81 / 85, 1101 x 605 200 / 169 / 174 / 272,
+//   1024^2 293 / 221 / 229 / 293, 1448^2 608 / 476 / 478 / -, 2048^2 1115 / 894 / 860 / -.
+// The whole-tile kernel runs one workgroup per CU, in rounds of 256 tiles of
+// about 18 us, against the marching kernel's chain of a state pass and a long
+// march: it wins while its tiles take at most two rounds.
+int lbmi_default_adj_variant(int nx, int ny)
 {
-    const int want[4] = {cells >= (1 << 20) ? 64 : 4, 18, 2, cells >= (1 << 20) ? 2 : 1};
+    const int64_t tiles = ((int64_t)nx + 63) / 64 * (((int64_t)ny + 3) / 4);
+    const bool big = (int64_t)nx * ny >= 3 * (1ll << 20) / 2;
+    const int tile_v[4] = {4, 18, 3, 0}, march_v[4] = {big ? 64 : 32, 18, 2, 2};
+    const int* want = tiles <= 512 ? tile_v : march_v;
     for (int v = 0; v < adj_variant_count(); ++v) {
         int d[4];
         adj_variant_desc(v, d);

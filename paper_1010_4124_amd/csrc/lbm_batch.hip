@@ -278,10 +278,12 @@ struct lbm_batch {
     int nwork = 0, ntiles = 0;
     BatchInst* inst = nullptr;
     int2* work = nullptr;
-    int work_cap = 0, ke_cap = 0;
-    int ke_rows = 1;  // rows of ke_part: steps of a graph whose energy partials one launch reduces
+    int work_cap = 0;
+    int64_t ke_cap = 0;  // (sum, max) pairs that ke_part holds
+    int ke_parts = 1;    // partials of one step of the current variant
+    int ke_rows = 1;     // steps of a graph whose energy partials one launch reduces
     double* scratch = nullptr;
-    double* ke_part = nullptr;  // [ke_rows][ke_cap][2] energy partials
+    double* ke_part = nullptr;  // [ke_rows][ke_parts][2] energy partials
     double* ke_ring = nullptr;  // [n][graph_chunk][2]
     double* msum = nullptr;     // 2 x (4 * cells): carried moment sums, ping-pong
     double* gbuf = nullptr;     // outflow ghost arrays of the instances that have them
@@ -370,6 +372,8 @@ int build_tables(lbm_batch* b)
         return bhip(e, "batch tables");
     b->nwork = (int)nwork;
     b->ntiles = (int)ntiles;
+    b->ke_parts = (int)std::max(ntiles, nblk);
+    b->ke_rows = (int)std::max<int64_t>(1, std::min<int64_t>(32, b->ke_cap / b->ke_parts));
     return LBM_OK;
 }
 
@@ -378,7 +382,7 @@ int build_tables(lbm_batch* b)
 hipError_t launch_batch_step(lbm_batch* b, const double* src, double* dst, bool ke, int parity,
                              hipStream_t st, int row = 0)
 {
-    double* part = b->ke_part + 2 * (int64_t)b->ke_cap * row;
+    double* part = b->ke_part + 2 * (int64_t)b->ke_parts * row;
     const BatchVariant& V = kBatchVariants[b->variant];
     // outflow ghosts of the state this step starts from, all instances at
     // once (with a state pass, that pass writes them)
@@ -429,7 +433,7 @@ hipError_t launch_batch_reduce(lbm_batch* b, double* out, int64_t stride, int64_
                                hipStream_t st, int rows = 1)
 {
     hipLaunchKernelGGL(k_reduce_batch, dim3(b->n, rows), dim3(256), 0, st, b->ke_part, b->inst,
-                       out, stride, pos, 2 * (int64_t)b->ke_cap);
+                       out, stride, pos, 2 * (int64_t)b->ke_parts);
     return hipGetLastError();
 }
 
@@ -553,7 +557,7 @@ static int batch_create_impl(const lbm_params* inst, int32_t n, const int64_t* f
         return bhip(e, "hipGetDevice");
     }
     // capacity for the variant with the most work items and the most tiles
-    int64_t wmax = 0, tmax = 0;
+    int64_t wmax = 0, tmax = 0, tall = 0;  // (tall: tiles of two rows or more)
     for (int v = 0; v < step_variant_count(); ++v) {
         int64_t w = 0, t = 0;
         for (int i = 0; i < n; ++i) {
@@ -564,10 +568,12 @@ static int batch_create_impl(const lbm_params* inst, int32_t n, const int64_t* f
         }
         wmax = std::max(wmax, w);
         tmax = std::max(tmax, t);
+        if (kBatchVariants[v].R > 1) tall = std::max(tall, t);
     }
     int64_t blocks = 0;
     for (int i = 0; i < n; ++i) blocks += ((int64_t)inst[i].nx * inst[i].ny + 255) / 256;
     tmax = std::max(tmax, blocks);
+    tall = std::max(tall, blocks);
     if (wmax >= (1ll << 31) || tmax >= (1ll << 30)) {
         delete b;
         return bfail(LBM_EINVAL, "batch too large");
@@ -578,13 +584,13 @@ static int batch_create_impl(const lbm_params* inst, int32_t n, const int64_t* f
             if (inst[i].bc[q] == LBM_BC_OUTFLOW) gtotal += NV * (int64_t)(q < 2 ? inst[i].ny : inst[i].nx);
     b->gcap = gtotal;
     b->work_cap = (int)wmax;
-    b->ke_cap = (int)std::max<int64_t>(tmax, 2 * NV);
-    // rows of partials for graph steps: up to 32, within 64 MiB
-    b->ke_rows = (int)std::max<int64_t>(
-        1, std::min<int64_t>(32, (int64_t)(64 << 20) / (16 * (int64_t)b->ke_cap)));
+    // energy partials: one step of any variant, 32 steps (of a graph) of those
+    // with tiles of two rows or more, within 64 MiB
+    b->ke_cap = std::max<int64_t>(
+        {tmax, 2 * NV, std::min<int64_t>(32 * tall, std::max<int64_t>(tall, (64 << 20) / 16))});
     b->hinst.resize(n);
     if ((e = hipMalloc(&b->scratch, sizeof(double) * (size_t)b->f_extent)) != hipSuccess ||
-        (e = hipMalloc(&b->ke_part, sizeof(double) * 2 * (size_t)b->ke_cap * b->ke_rows)) !=
+        (e = hipMalloc(&b->ke_part, sizeof(double) * 2 * (size_t)b->ke_cap)) !=
             hipSuccess ||
         (e = hipMalloc(&b->inst, sizeof(BatchInst) * (size_t)n)) != hipSuccess ||
         (e = hipMalloc(&b->work, sizeof(int2) * (size_t)b->work_cap)) != hipSuccess ||

@@ -13,11 +13,10 @@ struct lbm_ctx {
     int device = 0;
     int variant = 0;
     int adj_variant = 0;
-    int ke_cap = 0;   // partials per row of ke_part
-    int ke_rows = 1;  // rows of ke_part: steps whose energy partials one launch reduces
+    int64_t ke_cap = 0;  // (sum, max) pairs that ke_part holds
     lbmd::Consts k;                // per-context constants (kernel arguments)
     double* scratch = nullptr;     // 19 planes: ping-pong state of multi-step calls
-    double* ke_part = nullptr;     // [ke_rows][ke_cap][2] diagnostic partials
+    double* ke_part = nullptr;     // diagnostic partials of up to 32 steps
     double* colbuf = nullptr;      // nx doubles: column sums of lbm_sep_project
     double* msum = nullptr;        // 2 x [4][ny][nx]: carried moment sums (ping-pong)
     double* gbuf = nullptr;        // outflow ghosts: [19][ny] per x side, [19][nx] per y side
@@ -30,7 +29,7 @@ void lbmi_fill_consts(const lbm_params* p, lbmd::Consts* h);
 int lbmi_default_variant(int nx, int ny);
 int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4);
 int lbmi_tile_rows(int64_t t1, int64_t t2);  // rows of a whole-tile step's tiles
-int lbmi_default_adj_variant(int64_t cells);
+int lbmi_default_adj_variant(int nx, int ny);
 void lbmi_set_error(const char* msg);
 
 namespace lbmd {

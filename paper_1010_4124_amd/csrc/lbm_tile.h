@@ -103,17 +103,22 @@ struct TileWg {
 constexpr int TILE_MAX_NX = 1 << 24;
 constexpr unsigned TILE_SKIP = 0x80000000u;
 
+__device__ __forceinline__ unsigned uniform(int v)
+{
+    return (unsigned)__builtin_amdgcn_readfirstlane(v);
+}
+// (p and bytes are the same for all lanes; saying so keeps the compiler, which
+// may hold them in vector registers, from looping over their values)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const double* p, int bytes)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), 0, bytes, 0x00020000);
+    const unsigned long long u = (unsigned long long)p;
+    const unsigned lo = uniform((int)(unsigned)u), hi = uniform((int)(unsigned)(u >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void*)((unsigned long long)hi << 32 | lo), 0,
+                                             (int)uniform(bytes), 0x00020000);
 }
 __device__ __forceinline__ double row_load(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s)
 {
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, v, s, 0));
-}
-__device__ __forceinline__ unsigned uniform(int v)
-{
-    return (unsigned)__builtin_amdgcn_readfirstlane(v);
 }
 template <bool NT>
 __device__ __forceinline__ void row_store(double x, __amdgpu_buffer_rsrc_t r, unsigned v,
