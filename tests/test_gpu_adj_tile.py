@@ -53,3 +53,17 @@ def test_default_variants():
     for n, chunk in ((512, 32), (2048, 64)):
         c = lbm.Context(n, n, 1e-3, 1e-3, 1e-5, 1e-5)
         assert lbm.lbm_adjoint_variant_info(c.adj_variant) == (chunk, 18, 2, 2)
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (63, 15), (64, 16), (65, 17), (130, 63), (129, 64),
+                                   (200, 65), (67, 130)])
+def test_sep_project_sizes(shape):
+    """Column sums by 16 waves, four rows at a time: every remainder of rows and
+    columns. n = nx ny products and sums: within n 2^-53 of the sum of their sizes."""
+    nx, ny = shape
+    rng = np.random.default_rng(nx * 1000 + ny)
+    g, A, B = rng.normal(size=(ny, nx)), rng.normal(size=(3, nx)), rng.normal(size=ny)
+    ctx = lbm.Context(nx, ny, 1e-3, 1e-3, 1e-5, 1e-5)
+    got = ctx.sep_project(torch.from_numpy(g).cuda(), A, B).cpu().numpy()
+    t = A[:, None, :] * B[None, :, None] * g[None]
+    assert (np.abs(got - t.sum((1, 2))) <= (nx * ny + 4) * 2.0 ** -53 * np.abs(t).sum((1, 2))).all()
