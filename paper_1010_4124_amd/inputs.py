@@ -82,14 +82,10 @@ def mode_basis(nx, dx):
         raise ValueError("mode basis needs an even nx")
     L = nx * dx
     x = (np.arange(nx) + 0.5) * dx
-    rows, labels = [], []
-    for m in range(nx // 2):
-        rows.append(np.cos(2.0 * np.pi * m * x / L))
-        labels.append(("cos", m))
-    for m in range(1, nx // 2 + 1):
-        rows.append(np.sin(2.0 * np.pi * m * x / L))
-        labels.append(("sin", m))
-    return np.array(rows), labels
+    m = np.arange(nx // 2 + 1)[:, None]
+    arg = 2.0 * np.pi * m * x / L
+    labels = [("cos", q) for q in range(nx // 2)] + [("sin", q) for q in range(1, nx // 2 + 1)]
+    return np.concatenate([np.cos(arg[:-1]), np.sin(arg[1:])]), labels
 
 
 def mode_amplitudes(nx, seed, base=1e-3):
@@ -107,13 +103,14 @@ def mode_amplitudes(nx, seed, base=1e-3):
 
 
 def khi(nx=512, ny=512, dx=1e-3, dy=1e-3, dt=1e-5, tau=1e-5, Dv=0.02, Drho=0.02,
-        rho1=5.0, rho2=2.0, u0=0.5, p0=2.5, amps=None, pert=1e-3, yw=0.02):
+        rho1=5.0, rho2=2.0, u0=0.5, p0=2.5, amps=None, pert=1e-3, yw=0.02, basis=None):
     """Shear layer periodic in x with reflecting walls in y.
 
     rho(y) = (rho1 + rho2)/2 - (rho1 - rho2)/2 tanh(y / Drho),
     ux(y)  = u0 tanh(y / Dv), uniform p0 so T = p0 / rho,
     uy     = g(y) * sum_m a_m phi_m(x) with g(y) = exp(-(y / yw)^2);
-    without `amps` the perturbation is pert * sin(2 pi x / L_x) g(y).
+    without `amps` the perturbation is pert * sin(2 pi x / L_x) g(y). basis:
+    the rows of mode_basis(nx, dx), where the caller keeps them.
     """
     x, y = khi_coords(nx, ny, dx, dy)
     rho1d = 0.5 * (rho1 + rho2) - 0.5 * (rho1 - rho2) * np.tanh(y / Drho)
@@ -122,7 +119,7 @@ def khi(nx=512, ny=512, dx=1e-3, dy=1e-3, dt=1e-5, tau=1e-5, Dv=0.02, Drho=0.02,
     if amps is None:
         px = pert * np.sin(2.0 * np.pi * x / (nx * dx))
     else:
-        A, _ = mode_basis(nx, dx)
+        A = mode_basis(nx, dx)[0] if basis is None else basis
         px = np.asarray(amps, dtype=np.float64) @ A
     rho = np.repeat(rho1d[:, None], nx, axis=1)
     ux = np.repeat(ux1d[:, None], nx, axis=1)
@@ -159,14 +156,16 @@ def khi_paper(nx=600, ny=200, dx=1e-3, dy=1e-3, dt=1e-5, tau=1e-5, Dv=4e-3, Drho
                            k=k), ke_axis=1)
 
 
-def khi_tangents(nx, ny, dx, dy, Dv, Drho, rho1=5.0, rho2=2.0, u0=0.5, p0=2.5, yw=0.02):
+def khi_tangents(nx, ny, dx, dy, Dv, Drho, rho1=5.0, rho2=2.0, u0=0.5, p0=2.5, yw=0.02,
+                 basis=None):
     """Derivatives of the shear-layer initial fields with respect to the
     layer widths and the mode amplitudes, in separable form:
 
       d rho / d Drho = r(y),   d T / d Drho = t(y),   d ux / d Dv = v(y),
       d uy  / d a_m  = A[m, x] g(y).
 
-    Returns dict(r, t, v, g, A) of 1-D profiles and the mode matrix."""
+    Returns dict(r, t, v, g, A) of 1-D profiles and the mode matrix (basis, if
+    the caller keeps the rows of mode_basis(nx, dx))."""
     x, y = khi_coords(nx, ny, dx, dy)
     sech2 = lambda s: 1.0 / np.cosh(s) ** 2  # noqa: E731
     rho1d = 0.5 * (rho1 + rho2) - 0.5 * (rho1 - rho2) * np.tanh(y / Drho)
@@ -174,7 +173,7 @@ def khi_tangents(nx, ny, dx, dy, Dv, Drho, rho1=5.0, rho2=2.0, u0=0.5, p0=2.5, y
     t = -p0 / rho1d ** 2 * r
     v = u0 * sech2(y / Dv) * (-y / Dv ** 2)
     g = np.exp(-(y / yw) ** 2)
-    A, _ = mode_basis(nx, dx) if nx % 2 == 0 else (None, None)
+    A = basis if basis is not None else mode_basis(nx, dx)[0] if nx % 2 == 0 else None
     return {"r": r, "t": t, "v": v, "g": g, "A": A}
 
 

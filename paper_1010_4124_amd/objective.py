@@ -71,15 +71,22 @@ class KHIProblem:
         self.bc = (inputs.PERIODIC, inputs.PERIODIC, inputs.REFLECT, inputs.REFLECT)
         self.ctx = lbm.Context(nx, ny, dx, dy, dt, tau, self.bc)
         self._ctx2 = None  # the recompute context of the overlapped gradient
+        self._basis = None  # the mode basis of the grid, formed on first use
         if variant is not None:
             self.ctx.variant = variant
 
     def weight(self, n):
         return self.dt if self.n0 <= n <= self.n1 else 0.0
 
+    def basis(self):
+        if self._basis is None:
+            self._basis = inputs.mode_basis(self.nx, self.dx)[0]
+        return self._basis
+
     def fields(self, Dv, Drho, amps):
         return inputs.khi(self.nx, self.ny, self.dx, self.dy, self.dt, self.tau, Dv=float(Dv),
-                          Drho=float(Drho), amps=np.asarray(amps, dtype=np.float64), **self.phys)
+                          Drho=float(Drho), amps=np.asarray(amps, dtype=np.float64),
+                          basis=self.basis(), **self.phys)
 
     # -- forward ---------------------------------------------------------------
     def run(self, Dv, Drho, amps, keep_checkpoints=True):
@@ -148,24 +155,21 @@ class KHIProblem:
                     states.append(ctx.step(states[-1], 1))
             yield states, sums
 
-    # grids from this many cells on fill the GPU alone: no overlapped recompute
-    OVERLAP_MAX_CELLS = 1 << 20
-
     def gradient(self, Dv, Drho, amps, ck=None, scale=1.0, overlap=None):
         """(dJ/dD_v, dJ/dD_rho, dJ/da) by the discrete adjoint.
 
         overlap: recompute the next unit's states on a second context and
         stream while the current unit's reverse steps run (the two are
-        independent), so that grids too small to fill the GPU alone share it;
-        at most one more unit's states and one more segment's level-2
-        checkpoints are alive. The result is the same bit for bit. None (the
-        default): overlap below OVERLAP_MAX_CELLS cells only. On larger grids
-        the overlap gains little, and the states it frees on one stream after
-        use on the other are not reused by torch's caching allocator soon
-        enough: at 2048^2 x 4000 steps it reserved 250 GB for 45 GB in use,
-        and a 40000-step gradient ran out of room and slowed down."""
-        if overlap is None:
-            overlap = self.nx * self.ny < self.OVERLAP_MAX_CELLS
+        independent); at most one more unit's states and one more segment's
+        level-2 checkpoints are alive. The result is the same bit for bit. None (the
+        default): no overlap. Both steps fill the GPU by themselves from 64 x 48
+        cells on (whole-tile kernels, a workgroup or two on every CU), so the
+        second stream only adds its host work and events (us per step of a
+        400-step gradient, overlapped / not: 64 x 48 43 / 32, 256^2 54 / 41,
+        512^2 113 / 110, 1000^2 492 / 432); at 2048^2 the states it frees on one
+        stream after use on the other are not reused by torch's caching
+        allocator soon enough either (250 GB reserved for 45 GB in use)."""
+        overlap = bool(overlap)
         if ck is None:
             _, ck = self.run(Dv, Drho, amps)
         ctx = self.ctx
@@ -223,6 +227,7 @@ class KHIProblem:
         s = self.fields(Dv, Drho, amps)
         g_rho, g_ux, g_uy, g_T = ctx.init_vjp(*s.fields(), lam)
         t = inputs.khi_tangents(self.nx, self.ny, self.dx, self.dy, float(Dv), float(Drho),
+                                basis=self.basis(),
                                 **{k: self.phys[k] for k in ("rho1", "rho2", "u0", "p0", "yw")})
         ones = np.ones((1, self.nx))
         dDv = ctx.sep_project(g_ux, ones, t["v"])[0]
