@@ -445,16 +445,19 @@ int lbm_get_step_variant(lbm_ctx* c, int32_t* v)
 // batch), as measured on MI355X (microseconds per step, shear layers):
 //  - A whole-tile step takes the latency of one tile while all its workgroups
 //    are resident at once (two per CU: 512), less for lower tiles: 128^2 takes
-//    7.5 with R = 1 (256 tiles), 8.4 with R = 2, 10.8 with R = 4 (state pass and
-//    plane kernel: 12.2); 256^2 15.1, 11.5 (512 tiles), 11.7 (17.0).
+//    7.5 with R = 1 (256 tiles), 8.3 with R = 2, 10.7 with R = 4 (state pass and
+//    plane kernel: 12.2); 256^2 14.2, 10.9 (512 tiles), 11.9 (17.0).
 //  - Beyond that R = 4, which reads the fewest halo rows: 512^2 27.4 against
-//    32.2 with R = 2 and 37.0 for state pass and plane kernel.
+//    30.2 with R = 2 and 37.0 for state pass and plane kernel. Non-temporal
+//    stores from 2^20 cells on, where two states exceed the 256 MB cache:
+//    1448^2 195 against 206, a batch of 1.45 M cells 193 against 199; below,
+//    the next step finds the state there (1101 x 605 71 against 68, four
+//    outflow grids of 600 x 200 69 against 59).
 //  - The fast-tile kernel moves more bytes but keeps the chip busier. Its
-//    2048 wavefronts take the tiles in rounds, of about 40 us, and the band
-//    tiles at the grid's edge take 85 us: it wins from two full rounds on
-//    (1024^2: 97 against 102; 2048^2: 320 against 390; the 64-instance sweep
-//    of 20768 tiles: 480 against 565), unless the last round is nearly empty
-//    (1448^2, 4.07 rounds: 231 against 210; 1101 x 605, 1.3: 102 against 67).
+//    2048 wavefronts take the tiles in rounds of about 41 us, the whole-tile
+//    kernel 2048 tiles in 45: it wins from two rounds on if they are 90% full
+//    (1024^2 98 against 97; 2048^2 327 against 365; the 64-instance sweep of
+//    20768 tiles 480 against 550; not 1448^2, 4.07 rounds, 230 against 195).
 int lbmi_tile_rows(int64_t t1, int64_t t2)
 {
     constexpr int64_t RESIDENT = 512;
@@ -465,8 +468,9 @@ int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4)
 {
     constexpr int64_t ROUND = 2048;
     const int64_t rounds = (t4 + ROUND - 1) / ROUND;
-    const bool fast = t4 >= 2 * ROUND && 100 * t4 >= 84 * ROUND * rounds;
-    const int tile_v[6] = {lbmi_tile_rows(t1, t2), 18, 6, 1, 0, 0}, fast_v[6] = {4, 1, 2, 1, 1, 3};
+    const bool fast = t4 >= 2 * ROUND && 10 * t4 >= 9 * ROUND * rounds;
+    const int tile_v[6] = {lbmi_tile_rows(t1, t2), 18, 6, 1, t4 >= 4096, 0};
+    const int fast_v[6] = {4, 1, 2, 1, 1, 3};
     const int* want = fast ? fast_v : tile_v;
     for (int v = 0; v < step_variant_count(); ++v) {
         int d[6];

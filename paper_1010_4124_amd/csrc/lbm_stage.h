@@ -101,7 +101,7 @@ __device__ __forceinline__ void x_source_g(const GridBC& g, int gx, int& col, in
 // wide grid a row-major walk moves on before they are reused (at 2048 cells
 // wide and 4-row tiles, one tile row of the reverse step touches ~6.5 MB,
 // more than an XCD's 4 MB L2). Grids at most STRIP tiles wide are walked row
-// by row. Returns the tile's row-major index ty * tiles_x + tx.
+// by row. strip_walk returns the tile's row-major index ty * tiles_x + tx.
 // The fast-tile forward step walks strips of FAST_STRIP tile columns (2048
 // cells): on the 2048-wide grid that is a row-by-row walk, which measured
 // faster for it than strips of 8 or 16 tile columns.
@@ -116,6 +116,22 @@ __device__ __forceinline__ int strip_walk(int t, int tiles_x, int tiles_y)
     const int i = t - s * SW * tiles_y;
     const int ty = i / w;
     return ty * tiles_x + s * SW + (i - ty * w);
+}
+
+// The same walk as tile row and column, with one division on grids of one strip.
+struct TileXY {
+    int ty, tx;
+};
+__device__ __forceinline__ TileXY strip_walk_xy(int t, int tiles_x, int tiles_y)
+{
+    int s = 0, i = t, w = tiles_x;
+    if (tiles_x > STRIP) {
+        s = t / (STRIP * tiles_y);
+        w = min(STRIP, tiles_x - s * STRIP);
+        i = t - s * STRIP * tiles_y;
+    }
+    const int ty = i / w;
+    return TileXY{ty, s * STRIP + (i - ty * w)};
 }
 
 // v mapped once around a periodic axis of n >= the halo depth: the column

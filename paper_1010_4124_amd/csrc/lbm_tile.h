@@ -200,10 +200,10 @@ __device__ __forceinline__ void tile_load(const Grid& g, const TileConsts& k, co
         const __amdgpu_buffer_rsrc_t ry =
             rows_rsrc(fin + v.iy * plane + (int64_t)(y0 - HALO) * nx, (R + 2 * HALO) * rb);
         const int s0 = v.negy ? (R + 5) * rb : 0, sd = v.negy ? -rb : rb;
-        L.h = row_load(ry, hl ? (unsigned)((yhm + HALO) * rb + 8 * wrap_once(yhx, nx)) : TILE_SKIP,
-                       0);
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) L.p[j] = row_load(ry, vx8, uniform(s0 + j * sd));
+        L.h = row_load(ry, hl ? (unsigned)((yhm + HALO) * rb + 8 * wrap_once(yhx, nx)) : TILE_SKIP,
+                       0);
         if (v.hasn) {
             const __amdgpu_buffer_rsrc_t rn =
                 rows_rsrc(fin + v.in * plane + (int64_t)y0 * nx, R * rb);
@@ -303,6 +303,9 @@ __device__ __forceinline__ void tile_step(const Grid& g, const TileConsts& k, do
 
     TileRegs<R> L;
     tile_load<R, FAST>(g, k, v, tile_lane(), L);
+    // the constants' lines into the scalar cache while the planes are on their way
+    asm volatile("" ::"s"(k.s[0].vh), "s"(k.s[0].Fbc), "s"(k.s[1].ek), "s"(k.s[2].vh),
+                 "s"(k.s[2].Fc4));
     int lane = tile_lane();
     const int nx = g.nx(), ny = g.ny(), rb = 8 * nx;
     const int64_t plane = (int64_t)nx * ny;
@@ -537,10 +540,10 @@ __device__ __forceinline__ void tile_block(const TileArgs& a, double* lds)
     const int b = blockIdx.x;
     const int work = (b & 7) * a.per_xcd + (b >> 3);
     if (work >= a.nwork) return;
-    const int tile = strip_walk(work, a.s.tiles_x, a.tiles_y);
-    const int ty = tile / a.s.tiles_x, tx = tile - ty * a.s.tiles_x;
+    const TileXY t = strip_walk_xy(work, a.s.tiles_x, a.tiles_y);
     tile_any<R, NT, SCHEME>(
-        TileOfGrid{a, tx * TX, ty * R, a.ke_part ? a.ke_part + 2 * tile : nullptr}, a.k, lds);
+        TileOfGrid{a, t.tx * TX, t.ty * R,
+                   a.ke_part ? a.ke_part + 2 * (t.ty * a.s.tiles_x + t.tx) : nullptr}, a.k, lds);
 }
 
 }  // namespace lbmd
