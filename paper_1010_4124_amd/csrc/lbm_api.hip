@@ -338,7 +338,8 @@ int lbm_step_sums(lbm_ctx* c, const double* f_in, const double* sums_in, double*
     hipStream_t st = (hipStream_t)stream;
     const lbm_params& p = c->p;
     int info[6];
-    step_variant_desc(c->variant, info);
+    const int variant = lbmi_sums_variant(c->variant, n);
+    step_variant_desc(variant, info);
     const bool carry = p.scheme == LBM_SCHEME_WENO5 && (info[5] == 1 || info[5] == 3);
     if (!carry) {
         // the step as lbm_step takes it, then the sums of its result
@@ -355,7 +356,7 @@ int lbm_step_sums(lbm_ctx* c, const double* f_in, const double* sums_in, double*
         e = launch_outflow(f_in, p.nx, p.ny, c->gb, c->k, st);
         if (e != hipSuccess) return hip_fail(e, "lbm_step_sums outflow");
     }
-    e = launch_step(c->variant, f_in, f_out, c->k, nullptr, p.nx, p.ny, p.bc, p.dt / p.dx,
+    e = launch_step(variant, f_in, f_out, c->k, nullptr, p.nx, p.ny, p.bc, p.dt / p.dx,
                     p.dt / p.dy, p.dt / p.tau, p.ke_axis, c->gb, sums_in, sums_out, st, own);
     return e == hipSuccess ? LBM_OK : hip_fail(e, "lbm_step_sums");
 }
@@ -444,34 +445,29 @@ int lbm_get_step_variant(lbm_ctx* c, int32_t* v)
 // from the numbers of 64 x 1, 64 x 2 and 64 x 4 tiles (over all instances of a
 // batch), as measured on MI355X (microseconds per step, shear layers):
 //  - A whole-tile step takes the latency of one tile while all its workgroups
-//    are resident at once (two per CU: 512), less for lower tiles: 128^2 takes
-//    7.5 with R = 1 (256 tiles), 8.3 with R = 2, 10.7 with R = 4 (state pass and
-//    plane kernel: 12.2); 256^2 14.2, 10.9 (512 tiles), 11.9 (17.0).
-//  - Beyond that R = 4, which reads the fewest halo rows: 512^2 27.4 against
+//    are resident at once, less for lower tiles: 128^2 takes 7.5 with R = 1
+//    (256 tiles), 8.3 with R = 2, 11.5 with R = 4 (state pass and plane kernel:
+//    12.2); 256^2 14.2, 10.9 (512 tiles), 12.4 (17.0).
+//  - Beyond that R = 4, which reads the fewest halo rows: 512^2 25.9 against
 //    30.2 with R = 2 and 37.0 for state pass and plane kernel. Non-temporal
 //    stores from 2^20 cells on, where two states exceed the 256 MB cache:
-//    1448^2 195 against 206, a batch of 1.45 M cells 193 against 199; below,
-//    the next step finds the state there (1101 x 605 71 against 68, four
-//    outflow grids of 600 x 200 69 against 59).
-//  - The fast-tile kernel moves more bytes but keeps the chip busier. Its
-//    2048 wavefronts take the tiles in rounds of about 41 us, the whole-tile
-//    kernel 2048 tiles in 45: it wins from two rounds on if they are 90% full
-//    (1024^2 98 against 97; 2048^2 327 against 365; the 64-instance sweep of
-//    20768 tiles 480 against 550; not 1448^2, 4.07 rounds, 230 against 195).
+//    2048^2 309 against 340; below, the next step finds the state there
+//    (1101 x 605 69 against 62, four outflow grids of 600 x 200 62 against 53).
+//  - The fast-tile kernel with its carried sums moves 400 B per cell instead of
+//    310, in rounds of 2048 tiles and with band tiles of 85 us at the grid's
+//    edge: 1024^2 97 against 88, 1448^2 230 against 180, 3000 x 1000 279 against
+//    247, a 64-instance sweep of 5.3 M cells 468-490 against 449-456. On large
+//    single grids of whole tile columns, which leave it little of either, it is
+//    level and then ahead: 2048^2 (8 rounds) 317 against 324, 4096^2 1180
+//    against 1250.
 int lbmi_tile_rows(int64_t t1, int64_t t2)
 {
     constexpr int64_t RESIDENT = 512;
     return t1 <= RESIDENT ? 1 : t2 <= RESIDENT ? 2 : 4;
 }
 
-int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4)
+static int variant_index(const int (&want)[6])
 {
-    constexpr int64_t ROUND = 2048;
-    const int64_t rounds = (t4 + ROUND - 1) / ROUND;
-    const bool fast = t4 >= 2 * ROUND && 10 * t4 >= 9 * ROUND * rounds;
-    const int tile_v[6] = {lbmi_tile_rows(t1, t2), 18, 6, 1, t4 >= 4096, 0};
-    const int fast_v[6] = {4, 1, 2, 1, 1, 3};
-    const int* want = fast ? fast_v : tile_v;
     for (int v = 0; v < step_variant_count(); ++v) {
         int d[6];
         step_variant_desc(v, d);
@@ -482,10 +478,31 @@ int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4)
     return 0;
 }
 
+int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4)
+{
+    return variant_index({lbmi_tile_rows(t1, t2), 18, 6, 1, t4 >= 4096, 0});
+}
+
+// The variant of lbm_step_sums: a whole-tile step is followed by a pass that
+// forms the sums of its result (184 B per cell), so from 2^21 cells on the
+// fast-tile kernel, which writes them with the state, takes its place (2048^2:
+// 320 us against 309 + 160; results are the same bit for bit).
+int lbmi_sums_variant(int v, int64_t cells)
+{
+    int d[6];
+    step_variant_desc(v, d);
+    const bool tile = d[1] == 18 && d[5] == 0;
+    return tile && cells >= (1ll << 21) ? variant_index({4, 1, 2, 1, 1, 3}) : v;
+}
+
 int lbmi_default_variant(int nx, int ny)
 {
-    const int64_t tx = ((int64_t)nx + 63) / 64;
-    return lbmi_default_variant_tiles(tx * ny, tx * ((ny + 1) / 2), tx * (((int64_t)ny + 3) / 4));
+    constexpr int64_t ROUND = 2048;
+    const int64_t tx = ((int64_t)nx + 63) / 64, t4 = tx * (((int64_t)ny + 3) / 4);
+    const int64_t rounds = (t4 + ROUND - 1) / ROUND;
+    if (nx % 64 == 0 && t4 >= 8 * ROUND && 10 * t4 >= 9 * ROUND * rounds)
+        return variant_index({4, 1, 2, 1, 1, 3});
+    return lbmi_default_variant_tiles(tx * ny, tx * (((int64_t)ny + 1) / 2), t4);
 }
 
 static int adjoint_step(lbm_ctx* c, const double* f_n, const double* sums_n,

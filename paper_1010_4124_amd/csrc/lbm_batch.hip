@@ -152,7 +152,7 @@ struct TileOfBatch {
 };
 
 template <int R, bool NT>
-__global__ __launch_bounds__((64 * TILE_WAVES)) __attribute__((amdgpu_waves_per_eu(6)))
+__global__ __launch_bounds__((64 * tile_waves(R))) __attribute__((amdgpu_waves_per_eu(6)))
 void k_step_batch_tile(BatchArgs a, TileConsts k)
 {
     __shared__ double lds[TileWg<R>::LDS];
@@ -424,7 +424,7 @@ hipError_t launch_batch_step(lbm_batch* b, const double* src, double* dst, bool 
     a.slots = b->slots > 0 ? std::min(b->slots, a.per_xcd) : a.per_xcd;
     a.k = b->k;
     if (V.M == PH_TILE) {
-        hipLaunchKernelGGL(V.tile, dim3(8 * a.per_xcd), dim3(64 * TILE_WAVES), 0, st, a,
+        hipLaunchKernelGGL(V.tile, dim3(8 * a.per_xcd), dim3(64 * tile_waves(V.R)), 0, st, a,
                            tile_consts(b->k));
         return hipGetLastError();
     }

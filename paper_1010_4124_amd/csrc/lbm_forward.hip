@@ -86,7 +86,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W))) void k_
 
 // The whole-tile variants (lbm_tile.h).
 template <int R, bool NT>
-__global__ __launch_bounds__((64 * TILE_WAVES)) __attribute__((amdgpu_waves_per_eu(6)))
+__global__ __launch_bounds__((64 * tile_waves(R))) __attribute__((amdgpu_waves_per_eu(6)))
 void k_step_tile(TileArgs a)
 {
     __shared__ double lds[TileWg<R>::LDS];
@@ -455,7 +455,7 @@ hipError_t launch_step(int variant, const double* fin, double* fout, const Const
     }
     if (V.M == PH_TILE) {
         const TileArgs t = tile_args(a.s, k, ke_part, V.R);
-        hipLaunchKernelGGL(V.tile, dim3(8 * t.per_xcd), dim3(64 * TILE_WAVES), 0, st, t);
+        hipLaunchKernelGGL(V.tile, dim3(8 * t.per_xcd), dim3(64 * tile_waves(V.R)), 0, st, t);
         return hipGetLastError();
     }
     a.nwork = a.s.tiles_x * a.tiles_y * (V.M == PH_CARRY ? 1 : V.G);

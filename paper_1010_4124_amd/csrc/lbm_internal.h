@@ -28,6 +28,7 @@ int lbmi_validate(const lbm_params* p);
 void lbmi_fill_consts(const lbm_params* p, lbmd::Consts* h);
 int lbmi_default_variant(int nx, int ny);
 int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4);
+int lbmi_sums_variant(int v, int64_t cells);  // the variant lbm_step_sums takes for v
 int lbmi_tile_rows(int64_t t1, int64_t t2);  // rows of a whole-tile step's tiles
 int lbmi_default_adj_variant(int nx, int ny);
 void lbmi_set_error(const char* msg);

@@ -18,7 +18,7 @@
 namespace lbmd {
 
 template <int R, int SCHEME>
-__global__ __launch_bounds__((64 * TILE_WAVES)) __attribute__((amdgpu_waves_per_eu(6)))
+__global__ __launch_bounds__((64 * tile_waves(R))) __attribute__((amdgpu_waves_per_eu(6)))
 void k_step_lo(TileArgs a)
 {
     __shared__ double lds[TileWg<R>::LDS];
@@ -47,7 +47,7 @@ hipError_t launch_step_lo(int scheme, int R, const double* fin, double* fout, co
                                              {k_step_lo<4, 1>, k_step_lo<4, 2>}};
     const TileArgs t = tile_args(s, k, ke_part, R);
     hipLaunchKernelGGL(kernels[R >> 1][scheme == 1 ? 0 : 1], dim3(8 * t.per_xcd),
-                       dim3(64 * TILE_WAVES), 0, st, t);
+                       dim3(64 * tile_waves(R)), 0, st, t);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 // lbm_tile.h -- one forward-Euler D2V19 FDLB step (Eq. (47) of
-// arXiv:1010.4124) of one 64 x R tile by one workgroup of 12 wavefronts that
-// holds all 18 moving planes of the tile at once: the device body of the
-// whole-tile step variants (PH_TILE).
+// arXiv:1010.4124) of one 64 x R tile by one workgroup of 12 (R = 4: 8)
+// wavefronts that holds all 18 moving planes of the tile at once: the device
+// body of the whole-tile step variants (PH_TILE).
 //
 // Every plane is loaded once: the rows a velocity's y faces need go to
 // registers, their R centre rows and the x halo to LDS. The moments of Eq. (10)
@@ -9,8 +9,8 @@
 // that forms them first nor sums carried from step to step: 19 planes read
 // (plus halo rows, found in L2) and 19 written, in one launch.
 //
-// Wave w takes one velocity with v_y != 0 (shell w / 4; the four directions
-// off the x axis). Waves 0-5 take one velocity on the x axis as well (no y
+// With 12 waves, wave w takes one velocity with v_y != 0 (shell w / 4; the four
+// directions off the x axis). Waves 0-5 take one velocity on the x axis as well (no y
 // faces), waves 6 .. 5+R one row of cells: moments, equilibrium data, rest
 // particle and energy. A workgroup's waves go to the four SIMDs of a CU in
 // turn, so 12 waves of about equal work keep them level.
@@ -30,13 +30,12 @@
 //
 // What bounds it: on small grids the latency of one tile (launch, loads,
 // faces, stores in sequence), hence the many waves and the low R; on large
-// ones the phases of the two workgroups that fit a CU (LDS 53 KB and 24 waves
-// at R = 4) overlap incompletely: VALU busy 62% of the time at 2048^2, with
-// HBM traffic of 314 B per cell of the 304 it cannot do without (the
-// fast-tile kernel: 416, but 78% of the issue slots used, 320 us against 390
-// there). Measured per step, against the state pass and plane kernel it
-// replaces: 400 x 4 7.5 us (12.6), 256^2 11.5 (17.0), 512^2 27.4 (37.0),
-// 1101 x 605 67 (101), four outflow grids of 600 x 200 in a batch 59 (76).
+// ones the phases of the workgroups that fit a CU overlap incompletely: with
+// the three of tile8_step (R = 4) VALU is busy 69% of the time at 2048^2, with
+// HBM traffic of 310 B per cell of the 304 it cannot do without (the fast-tile
+// kernel: 408). Measured per step, against the state pass and plane kernel it
+// replaces: 400 x 4 6.9 us (12.6), 256^2 10.8 (17.0), 512^2 26.4 (37.0),
+// 1101 x 605 63 (101), four outflow grids of 600 x 200 in a batch 53 (76).
 #pragma once
 
 #include "lbm_device.h"
@@ -82,6 +81,8 @@ __device__ __forceinline__ double weight_t(const TileShell& k, double T)
 }
 
 constexpr int TILE_WAVES = 12;
+// wavefronts of a tile's workgroup (tile_step, tile8_step)
+constexpr int tile_waves(int R) { return R == 4 ? 8 : TILE_WAVES; }
 template <int R>
 struct TileWg {
     static constexpr int PL = R * PITCH;        // one staged plane, later its x flux differences
@@ -169,20 +170,28 @@ __device__ __forceinline__ int halo_col(int hq, bool negx, int w)
     return negx ? w - 1 - c : c;
 }
 
-// What a wave loads of a tile.
-template <int R>
-struct TileRegs {
-    double p[R + 5], h;  // velocity off the axis: canonical rows, halo value
-    double pn[R], hn;    // velocity on it
-    double f0;           // rest plane, the wave's cell row
+// One moving velocity: its plane, shell and sense on each axis (hasy: v_y != 0).
+struct TileVel {
+    int i, s;
+    bool negx, negy, hasy;
 };
+// direction t of {0, 1, 3, 4} of shell s; velocity j of the six on the x axis
+__device__ __forceinline__ TileVel vel_y(int s, int t)
+{
+    return TileVel{1 + 6 * s + t + (t >= 2 ? 1 : 0), s, t == 1 || t == 2, t >= 2, true};
+}
+__device__ __forceinline__ TileVel vel_x(int j)
+{
+    const bool neg = (j & 1) == 0;  // directions 2 and 5
+    return TileVel{1 + 6 * (j >> 1) + (neg ? 2 : 5), j >> 1, neg, false, false};
+}
 
-// Request the wave's rows of tile g (FAST: a fast tile). Canonical row j of the
-// velocity off the axis is row y0-3 + j, or y0+R+2 - j for v_y < 0; cell row m
-// is j = m + 3.
+// Request a velocity's rows p and halo value h of tile g (FAST: a fast tile).
+// Canonical row j is row y0-3 + j, or y0+R+2 - j for v_y < 0; cell row m is
+// j = m + 3. Without y faces only the R cell rows are read.
 template <int R, bool FAST, class Grid>
-__device__ __forceinline__ void tile_load(const Grid& g, const TileConsts& k, const TileWave& v,
-                                          int lane, TileRegs<R>& L)
+__device__ __forceinline__ void vel_load(const Grid& g, const TileConsts& k, const TileVel& v,
+                                         int lane, double (&p)[R + 5], double& h)
 {
     const int x0 = g.x0, y0 = g.y0;
     constexpr int ROWS = R + 5;
@@ -190,75 +199,83 @@ __device__ __forceinline__ void tile_load(const Grid& g, const TileConsts& k, co
     const int64_t plane = (int64_t)nx * ny;
     const double* fin = g.fin();
     const int w = FAST ? 64 : min(64, nx - x0);
-    const unsigned l8 = 8u * (unsigned)lane, vx8 = l8 + 8u * (unsigned)x0;  // (vx8: fast tiles)
+    const unsigned l8 = 8u * (unsigned)lane, vx8 = l8 + 8u * (unsigned)x0;
     const bool hl = lane < 5 * R;
     const int hr = lane / 5, hq = lane - 5 * hr;
-    const int yhx = x0 + halo_col(hq, v.ynegx, w), nhx = x0 + halo_col(hq, v.nnegx, w);
-    const int yhm = v.negy ? R - 1 - hr : hr;
-    const bool hasm = v.m >= 0 && v.m < R;
+    const int hx = x0 + halo_col(hq, v.negx, w), hm = v.negy ? R - 1 - hr : hr;
     if constexpr (FAST) {
         const __amdgpu_buffer_rsrc_t ry =
-            rows_rsrc(fin + v.iy * plane + (int64_t)(y0 - HALO) * nx, (R + 2 * HALO) * rb);
+            rows_rsrc(fin + v.i * plane + (int64_t)(y0 - HALO) * nx, (R + 2 * HALO) * rb);
         const int s0 = v.negy ? (R + 5) * rb : 0, sd = v.negy ? -rb : rb;
+        if (v.hasy) {
 #pragma unroll
-        for (int j = 0; j < ROWS; ++j) L.p[j] = row_load(ry, vx8, uniform(s0 + j * sd));
-        L.h = row_load(ry, hl ? (unsigned)((yhm + HALO) * rb + 8 * wrap_once(yhx, nx)) : TILE_SKIP,
-                       0);
-        if (v.hasn) {
-            const __amdgpu_buffer_rsrc_t rn =
-                rows_rsrc(fin + v.in * plane + (int64_t)y0 * nx, R * rb);
-            L.hn = row_load(rn, hl ? (unsigned)(hr * rb + 8 * wrap_once(nhx, nx)) : TILE_SKIP, 0);
+            for (int j = 0; j < ROWS; ++j) p[j] = row_load(ry, vx8, uniform(s0 + j * sd));
+        } else {
 #pragma unroll
-            for (int j = 0; j < R; ++j) L.pn[j] = row_load(rn, vx8, uniform(j * rb));
+            for (int j = HALO; j < HALO + R; ++j) p[j] = row_load(ry, vx8, uniform(s0 + j * sd));
         }
+        h = row_load(ry, hl ? (unsigned)((hm + HALO) * rb + 8 * wrap_once(hx, nx)) : TILE_SKIP, 0);
     } else {
         const GridBC b = g.bc();
-        // mirror partners of directions 0, 1, 3, 4: (1, 0, 4, 3) and (4, 3, 1, 0)
-        const int s6 = 1 + 6 * v.sy, d = v.iy - s6;
-        const int ix = s6 + (d == 0 ? 1 : d == 1 ? 0 : d == 3 ? 4 : 3), im = s6 + 4 - d;
-        // a row's source is the same for all lanes
-#pragma unroll
-        for (int j = 0; j < ROWS; ++j) {
+        const int s6 = 1 + 6 * v.s, d = v.i - s6;
+        // mirror partners: directions 0 .. 5 in x (1, 0, 5, 4, 3, 2); in y (4, 3, -, 1, 0, -)
+        const int ix = s6 + (d == 0 ? 1 : d == 1 ? 0 : d == 2 ? 5 : d == 3 ? 4 : d == 4 ? 3 : 2);
+        const int im = s6 + 4 - d;
+        // halo values of the rows inside the domain
+        int col = 0, kind = CK_NONE;
+        const int hy = y0 + hm;
+        if (hl && hy < ny) x_source_g<false>(b, hx, col, kind);
+        const bool out = kind == CK_OUTLO || kind == CK_OUTHI;
+        const int64_t off = out ? (int64_t)v.i * ny + hy
+                                : (kind == CK_MIRX ? ix : v.i) * plane + (int64_t)hy * nx + col;
+        const double* base = kind == CK_OUTLO ? b.gb[XLO] : kind == CK_OUTHI ? b.gb[XHI] : fin;
+        const bool ld = kind == CK_NORM || kind == CK_MIRX || out;
+        const double x = base[ld ? off : 0];
+        const double c = kind == CK_CXLO ? g.side_eq(k, XLO, v.i) : g.side_eq(k, XHI, v.i);
+        h = ld ? x : kind == CK_NONE ? 0.0 : c;
+        auto row = [&](int j) {  // (a row's source is the same for all lanes)
             const RowDesc rd = row_desc_g<false>(b, v.negy ? y0 + R + 2 - j : y0 - HALO + j);
-            const double* src = fin + (rd.mode == RM_MIRY ? im : v.iy) * plane +
+            const double* src = fin + (rd.mode == RM_MIRY ? im : v.i) * plane +
                                 (int64_t)rd.src * nx;
             if (rd.mode == RM_OUT)
-                src = (rd.side == YLO ? b.gb[YLO] : b.gb[YHI]) + (int64_t)v.iy * nx;
-            const bool ld = rd.mode != RM_CONST && rd.mode != RM_NONE;
-            L.p[j] = row_load(rows_rsrc(src + x0, ld ? 8 * w : 0), l8, 0);
-        }
-        // halo values of the rows inside the domain
-        auto halo = [&](int i, int imx, int hx, int hy) {
-            int col = 0, kind = CK_NONE;
-            if (hl && hy < ny) x_source_g<false>(b, hx, col, kind);
-            const bool out = kind == CK_OUTLO || kind == CK_OUTHI;
-            const int64_t off = out ? (int64_t)i * ny + hy
-                                    : (kind == CK_MIRX ? imx : i) * plane + (int64_t)hy * nx + col;
-            const double* base = kind == CK_OUTLO ? b.gb[XLO] : kind == CK_OUTHI ? b.gb[XHI] : fin;
-            const bool ld = kind == CK_NORM || kind == CK_MIRX || out;
-            const double x = base[ld ? off : 0];
-            const double c = kind == CK_CXLO ? g.side_eq(k, XLO, i) : g.side_eq(k, XHI, i);
-            return ld ? x : kind == CK_NONE ? 0.0 : c;
+                src = (rd.side == YLO ? b.gb[YLO] : b.gb[YHI]) + (int64_t)v.i * nx;
+            const bool l = rd.mode != RM_CONST && rd.mode != RM_NONE;
+            return row_load(rows_rsrc(src + x0, l ? 8 * w : 0), l8, 0);
         };
-        L.h = halo(v.iy, ix, yhx, y0 + yhm);
-        if (v.hasn) {
+        if (v.hasy) {
 #pragma unroll
-            for (int j = 0; j < R; ++j)
-                L.pn[j] = row_load(
-                    rows_rsrc(fin + v.in * plane + (int64_t)min(y0 + j, ny - 1) * nx + x0, 8 * w),
-                    l8, 0);
-            L.hn = halo(v.in, 1 + 6 * v.sn + (v.nnegx ? 5 : 2), nhx, y0 + hr);
-        }
-        // rows of a fixed-equilibrium side
+            for (int j = 0; j < ROWS; ++j) p[j] = row(j);
 #pragma unroll
-        for (int j = 0; j < ROWS; ++j) {
-            const RowDesc rd = row_desc_g<false>(b, v.negy ? y0 + R + 2 - j : y0 - HALO + j);
-            if (rd.mode == RM_CONST) L.p[j] = g.side_eq(k, rd.side, v.iy);
+            for (int j = 0; j < ROWS; ++j) {  // rows of a fixed-equilibrium side
+                const RowDesc rd = row_desc_g<false>(b, v.negy ? y0 + R + 2 - j : y0 - HALO + j);
+                if (rd.mode == RM_CONST) p[j] = g.side_eq(k, rd.side, v.i);
+            }
+        } else {
+#pragma unroll
+            for (int j = HALO; j < HALO + R; ++j)
+                p[j] = row_load(rows_rsrc(fin + v.i * plane +
+                                              (int64_t)min(y0 + j - HALO, ny - 1) * nx + x0, 8 * w),
+                                l8, 0);
         }
     }
-    if (hasm)
-        L.f0 = row_load(rows_rsrc(fin + (int64_t)(y0 + v.m) * nx + x0,
-                                  FAST || y0 + v.m < ny ? 8 * w : 0), l8, 0);
+}
+
+// A velocity's R centre rows and x halo into its plane in LDS (w columns).
+template <int R, bool FAST>
+__device__ __forceinline__ void vel_stage(const TileVel& v, int w, int lane,
+                                          const double (&p)[R + 5], double h, double* lds)
+{
+    double* s = lds + (v.i - 1) * TileWg<R>::PL + HALO;
+    if (FAST || lane < w) {
+        const int c = v.negx ? 63 - lane : lane;
+#pragma unroll
+        for (int j = 0; j < R; ++j) s[j * PITCH + c] = p[j + HALO];
+    }
+    if (lane < 5 * R) {
+        const int hr = lane / 5, hq = lane - 5 * hr;
+        const int c = halo_col(hq, v.negx, w);
+        s[hr * PITCH + (v.negx ? 63 - c : c)] = h;
+    }
 }
 
 // Flux differences of f along a strip of R cells from its upwind-ordered
@@ -284,6 +301,103 @@ __device__ __forceinline__ void strip_diff(const double (&P)[R + 5], double eps,
     }
 }
 
+// The rest plane in the wave's cell row m.
+template <bool FAST, class Grid>
+__device__ __forceinline__ double rest_load(const Grid& g, int m, int w, int lane)
+{
+    const int nx = g.nx();
+    return row_load(rows_rsrc(g.fin() + (int64_t)(g.y0 + m) * nx + g.x0,
+                              FAST || g.y0 + m < g.ny() ? 8 * w : 0), 8u * (unsigned)lane, 0);
+}
+
+// The constants' lines into the scalar cache, while the planes are on their way.
+__device__ __forceinline__ void warm_consts(const TileConsts& k)
+{
+    asm volatile("" ::"s"(k.s[0].vh), "s"(k.s[0].Fbc), "s"(k.s[1].ek), "s"(k.s[2].vh),
+                 "s"(k.s[2].Fc4));
+}
+
+// Cell row m of the staged tile: moments, equilibrium data for the update,
+// rest particle, energy partial.
+template <int R, bool FAST, class Grid>
+__device__ __forceinline__ void tile_cells(const Grid& g, const TileConsts& k, int m, int wd,
+                                           double f0, double* lds)
+{
+    using S = TileWg<R>;
+    double* const st = lds + S::ST;
+    const int lane = tile_lane(), nx = g.nx(), ny = g.ny(), y0 = g.y0;
+    const bool inx = FAST || lane < wd, act = FAST || (inx && y0 + m < ny);
+    // the sums of k_sums, in its order
+    double r = 0.0, jx = 0.0, jy = 0.0, E = 0.0;
+    r += f0;
+    jx = __builtin_fma(f0, 0.0, jx);
+    jy = __builtin_fma(f0, 0.0, jy);
+    E = __builtin_fma(f0, 0.0, E);
+#pragma unroll
+    for (int i = 1; i < NV; ++i) {
+        const int d = (i - 1) % 6;
+        const TileShell& s = k.s[(i - 1) / 6];
+        const bool nx_ = dir_cos(d) < 0.0;
+        const int row = dir_sin_sign(d) < 0 ? R - 1 - m : m;
+        const double fi =
+            lds[(i - 1) * S::PL + row * PITCH + HALO + (nx_ ? 63 - lane : lane)];
+        const double vx = d == 2 || d == 5 ? s.vk : s.vh;
+        r += fi;
+        jx = __builtin_fma(fi, nx_ ? -vx : vx, jx);
+        jy = __builtin_fma(
+            fi, dir_sin_sign(d) > 0 ? s.vs : dir_sin_sign(d) < 0 ? -s.vs : 0.0, jy);
+        E = __builtin_fma(fi, s.h2, E);
+    }
+    if (!act) {  // idle lanes: unit state
+        r = E = 1.0;
+        jx = jy = 0.0;
+    }
+    const CellEq c = cell_eq_from_sums(r, jx, jy, E);
+    const double ct = g.ct(), rho = ct * c.rho;
+    const double F1 = weight_t(k.s[0], c.T), F2 = weight_t(k.s[1], c.T),
+                 F3 = weight_t(k.s[2], c.T);
+    double* sc = st + m * 64 + lane;
+    sc[0 * R * 64] = rho * F1;
+    sc[1 * R * 64] = rho * F2;
+    sc[2 * R * 64] = rho * F3;
+    sc[3 * R * 64] = c.uxt;
+    sc[4 * R * 64] = c.uyt;
+    sc[5 * R * 64] =
+        __builtin_fma(-0.5 * c.T, __builtin_fma(c.uxt, c.uxt, c.uyt * c.uyt), 1.0);
+    // rest particle: no convection, f^eq_0 = rho F_0 (1 - u^2/2T)
+    const double F0 = 1.0 - 6.0 * (F1 + F2 + F3);
+    const double fe = c.rho * F0 * c.t0;
+    row_store<false>(__builtin_fma(-ct, f0 - fe, f0),
+                     rows_rsrc(g.fout() + (int64_t)(y0 + m) * nx + g.x0,
+                               FAST || y0 + m < ny ? 8 * wd : 0), 8u * (unsigned)lane, 0);
+    if (g.ke) {
+        const double un = (g.ke_axis() ? jx : jy) / r;
+        const double e = act ? 0.5 * r * un * un : 0.0;
+        const double ke_s = wave_sum(e), ke_m = wave_max(e);
+        if (lane == 0) {
+            lds[S::KE + 2 * m] = ke_s;
+            lds[S::KE + 2 * m + 1] = ke_m;
+        }
+    }
+}
+
+// The tile's energy partial from those of its cell rows.
+template <int R, class Grid>
+__device__ __forceinline__ void tile_energy(const Grid& g, const double* lds)
+{
+    using S = TileWg<R>;
+    if (g.ke && threadIdx.x == 0) {
+        double s = lds[S::KE], mx = lds[S::KE + 1];
+#pragma unroll
+        for (int j = 1; j < R; ++j) {
+            s += lds[S::KE + 2 * j];
+            mx = fmax(mx, lds[S::KE + 2 * j + 1]);
+        }
+        g.ke[0] = s;
+        g.ke[1] = mx;
+    }
+}
+
 // Tile g (FAST: a fast tile) by one workgroup. g is a Grid (the accessors used
 // below) with the tile's origin x0, y0 and its energy partial ke (null: none
 // wanted). lds holds TileWg<R>::LDS doubles.
@@ -301,92 +415,26 @@ __device__ __forceinline__ void tile_step(const Grid& g, const TileConsts& k, do
     double* const s_n = lds + (v.in - 1) * S::PL;
     double* const st = lds + S::ST;
 
-    TileRegs<R> L;
-    tile_load<R, FAST>(g, k, v, tile_lane(), L);
-    // the constants' lines into the scalar cache while the planes are on their way
-    asm volatile("" ::"s"(k.s[0].vh), "s"(k.s[0].Fbc), "s"(k.s[1].ek), "s"(k.s[2].vh),
-                 "s"(k.s[2].Fc4));
+    const TileVel vy{v.iy, v.sy, v.ynegx, v.negy, true}, vn{v.in, v.sn, v.nnegx, false, false};
+    double p[ROWS], f0 = 0.0;
     int lane = tile_lane();
     const int nx = g.nx(), ny = g.ny(), rb = 8 * nx;
     const int64_t plane = (int64_t)nx * ny;
     const int y0 = g.y0, wd = FAST ? 64 : min(64, nx - g.x0);
-    // ---- stage
-    if (FAST || lane < wd) {
-        const int ylc = v.ynegx ? 63 - lane : lane, nlc = v.nnegx ? 63 - lane : lane;
-#pragma unroll
-        for (int j = 0; j < R; ++j) s_y[j * PITCH + HALO + ylc] = L.p[j + HALO];
-        if (v.hasn) {
-#pragma unroll
-            for (int j = 0; j < R; ++j) s_n[j * PITCH + HALO + nlc] = L.pn[j];
-        }
-    }
-    if (lane < 5 * R) {
-        const int hr = lane / 5, hq = lane - 5 * hr;
-        const int cy = halo_col(hq, v.ynegx, wd), cn = halo_col(hq, v.nnegx, wd);
-        s_y[hr * PITCH + HALO + (v.ynegx ? 63 - cy : cy)] = L.h;
-        if (v.hasn) s_n[hr * PITCH + HALO + (v.nnegx ? 63 - cn : cn)] = L.hn;
+    {
+        double h, pn[ROWS], hn;
+        vel_load<R, FAST>(g, k, vy, lane, p, h);
+        if (v.hasn) vel_load<R, FAST>(g, k, vn, lane, pn, hn);
+        if (hasm) f0 = rest_load<FAST>(g, v.m, wd, lane);
+        warm_consts(k);
+        lane = tile_lane();
+        vel_stage<R, FAST>(vy, wd, lane, p, h, lds);
+        if (v.hasn) vel_stage<R, FAST>(vn, wd, lane, pn, hn, lds);
     }
     __syncthreads();
 
     // ---- phase A
-    if (hasm) {
-        const int m = v.m;
-        lane = tile_lane();
-        const bool inx = FAST || lane < wd, act = FAST || (inx && y0 + m < ny);
-        const double f0 = L.f0;
-        // the sums of k_sums, in its order
-        double r = 0.0, jx = 0.0, jy = 0.0, E = 0.0;
-        r += f0;
-        jx = __builtin_fma(f0, 0.0, jx);
-        jy = __builtin_fma(f0, 0.0, jy);
-        E = __builtin_fma(f0, 0.0, E);
-#pragma unroll
-        for (int i = 1; i < NV; ++i) {
-            const int d = (i - 1) % 6;
-            const TileShell& s = k.s[(i - 1) / 6];
-            const bool nx_ = dir_cos(d) < 0.0;
-            const int row = dir_sin_sign(d) < 0 ? R - 1 - m : m;
-            const double fi =
-                lds[(i - 1) * S::PL + row * PITCH + HALO + (nx_ ? 63 - lane : lane)];
-            const double vx = d == 2 || d == 5 ? s.vk : s.vh;
-            r += fi;
-            jx = __builtin_fma(fi, nx_ ? -vx : vx, jx);
-            jy = __builtin_fma(
-                fi, dir_sin_sign(d) > 0 ? s.vs : dir_sin_sign(d) < 0 ? -s.vs : 0.0, jy);
-            E = __builtin_fma(fi, s.h2, E);
-        }
-        if (!act) {  // idle lanes: unit state
-            r = E = 1.0;
-            jx = jy = 0.0;
-        }
-        const CellEq c = cell_eq_from_sums(r, jx, jy, E);
-        const double ct = g.ct(), rho = ct * c.rho;
-        const double F1 = weight_t(k.s[0], c.T), F2 = weight_t(k.s[1], c.T),
-                     F3 = weight_t(k.s[2], c.T);
-        double* sc = st + m * 64 + lane;
-        sc[0 * R * 64] = rho * F1;
-        sc[1 * R * 64] = rho * F2;
-        sc[2 * R * 64] = rho * F3;
-        sc[3 * R * 64] = c.uxt;
-        sc[4 * R * 64] = c.uyt;
-        sc[5 * R * 64] =
-            __builtin_fma(-0.5 * c.T, __builtin_fma(c.uxt, c.uxt, c.uyt * c.uyt), 1.0);
-        // rest particle: no convection, f^eq_0 = rho F_0 (1 - u^2/2T)
-        const double F0 = 1.0 - 6.0 * (F1 + F2 + F3);
-        const double fe = c.rho * F0 * c.t0;
-        row_store<false>(__builtin_fma(-ct, f0 - fe, f0),
-                         rows_rsrc(g.fout() + (int64_t)(y0 + m) * nx + g.x0,
-                                   FAST || y0 + m < ny ? 8 * wd : 0), 8u * (unsigned)lane, 0);
-        if (g.ke) {
-            const double un = (g.ke_axis() ? jx : jy) / r;
-            const double e = act ? 0.5 * r * un * un : 0.0;
-            const double ke_s = wave_sum(e), ke_m = wave_max(e);
-            if (lane == 0) {
-                lds[S::KE + 2 * m] = ke_s;
-                lds[S::KE + 2 * m + 1] = ke_m;
-            }
-        }
-    }
+    if (hasm) tile_cells<R, FAST>(g, k, v.m, wd, f0, lds);
     lane = tile_lane();
     const int xr = lane % R, xs = lane / R;  // x strips: row, strip of R cells (x_pass)
     // The faces, one strip after the other: each result is pinned where it
@@ -406,21 +454,12 @@ __device__ __forceinline__ void tile_step(const Grid& g, const TileConsts& k, do
         strip_diff<R, SCHEME>(P, eps, dh);
         pin(dh);
     };
-    strip_diff<R, SCHEME>(L.p, ky.ey, dhy);
+    strip_diff<R, SCHEME>(p, ky.ey, dhy);
     pin(dhy);
     x_strip(s_y, ky.eh, dhx);
     if (v.hasn) x_strip(s_n, kn.ek, dhn);
     __syncthreads();
-    if (g.ke && threadIdx.x == 0) {
-        double s = lds[S::KE], mx = lds[S::KE + 1];
-#pragma unroll
-        for (int j = 1; j < R; ++j) {
-            s += lds[S::KE + 2 * j];
-            mx = fmax(mx, lds[S::KE + 2 * j + 1]);
-        }
-        g.ke[0] = s;
-        g.ke[1] = mx;
-    }
+    tile_energy<R>(g, lds);
 
     // ---- phase B: the cells' values, left to the staged planes so far,
     // then the x flux differences in their place
@@ -481,14 +520,145 @@ __device__ __forceinline__ void tile_step(const Grid& g, const TileConsts& k, do
     }
 }
 
+// The same by 8 wavefronts, for R = 4. Three such workgroups fit a CU (3 x 53 KB
+// of LDS, 24 waves at 80 registers) where 12 waves let two: one more tile's
+// loads and stores behind the others' faces. Waves 0-3 take two velocities off
+// the x axis, waves 4-7 one, one or two on it and a cell row; both kinds have
+// three plane loads, and a wave of each kind shares a SIMD. The x faces come
+// after the second barrier, one velocity at a time, to stay within 80
+// registers. Per step against 12 waves: 512^2 25.9 us (27.1), 1101 x 605 62.4
+// (66.4), 1024^2 86 (100), 1448^2 175 (196), 2048^2 309 (358; 4.2 TB/s, VALU
+// busy 69%), a batch of 1.45 M cells 167 (180); below one round, where only a
+// tile's latency counts, 600 x 200 24.1-24.7 (24.3).
+// Raised wave priority around the loads gives 6% at 1101 x 605 (66.2 to 62.4)
+// and 5% on four grids of 600 x 200, but costs as much on the states beyond the
+// cache (2048^2 309 to 325), which are the ones stored non-temporally.
+// Workgroups that stay and loop over tiles: 348 at 2048^2 (the next tile's loads
+// wait behind the last one's stores, as both are counted in order).
+template <int R, bool NT, bool FAST, int SCHEME, class Grid>
+__device__ __forceinline__ void tile8_step(const Grid& g, const TileConsts& k, double* lds)
+{
+    using S = TileWg<R>;
+    constexpr int ROWS = R + 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int t = wave & 3;
+    const TileVel va = vel_y(wave < 4 ? 0 : 2, wave & 3);
+    const int jn = wave == 5 ? 2 : wave == 6 ? 4 : wave == 7 ? 5 : 0;
+    const TileVel yb = vel_y(1, wave & 3), nb = vel_x(jn), vb = wave < 4 ? yb : nb;
+    const TileVel vc = vel_x(jn + 1);
+    const bool hasc = wave == 4 || wave == 5;
+    const int m = wave - 4;
+    double* const st = lds + S::ST;
+    const int nx = g.nx(), ny = g.ny(), rb = 8 * nx;
+    const int64_t plane = (int64_t)nx * ny;
+    const int y0 = g.y0, wd = FAST ? 64 : min(64, nx - g.x0);
+
+    // ---- load, stage, y faces
+    double f0 = 0.0, dya[R], dyb[R];
+    {
+        double pa[ROWS], pb[ROWS], ha, hb;
+        // the loads of a tile ahead of the faces of the CU's other two
+        if (!NT) __builtin_amdgcn_s_setprio(3);
+        const int lane = tile_lane();
+        vel_load<R, FAST>(g, k, va, lane, pa, ha);
+        if (m >= 0) f0 = rest_load<FAST>(g, m, wd, lane);
+        if (wave < 4) {
+            vel_load<R, FAST>(g, k, yb, lane, pb, hb);
+        } else {
+            double pn[ROWS], hn, pc[ROWS], hc = 0.0;
+            vel_load<R, FAST>(g, k, nb, lane, pn, hn);
+            if (hasc) vel_load<R, FAST>(g, k, vc, lane, pc, hc);
+            vel_stage<R, FAST>(nb, wd, lane, pn, hn, lds);
+            if (hasc) vel_stage<R, FAST>(vc, wd, lane, pc, hc, lds);
+        }
+        warm_consts(k);
+        vel_stage<R, FAST>(va, wd, lane, pa, ha, lds);
+        if (wave < 4) vel_stage<R, FAST>(yb, wd, lane, pb, hb, lds);
+        if (!NT) __builtin_amdgcn_s_setprio(0);
+        __syncthreads();
+        strip_diff<R, SCHEME>(pa, k.s[va.s].ey, dya);
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            asm volatile("" : "+v"(dya[q]));
+            dyb[q] = 0.0;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (wave < 4) strip_diff<R, SCHEME>(pb, k.s[1].ey, dyb);
+#pragma unroll
+        for (int q = 0; q < R; ++q) asm volatile("" : "+v"(dyb[q]));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (m >= 0) tile_cells<R, FAST>(g, k, m, wd, f0, lds);
+    __syncthreads();
+    tile_energy<R>(g, lds);
+
+    // ---- a velocity's x faces, update and stores
+    const double omct = 1.0 - g.ct();
+    auto finish = [&](const TileVel& v, const double (&dhy)[R]) {
+        const int lane = tile_lane();
+        const TileShell& ks = k.s[v.s];
+        double* s_p = lds + (v.i - 1) * S::PL;
+        const int lc = v.negx ? 63 - lane : lane;
+        double fc[R], P[ROWS], dh[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) fc[j] = s_p[j * PITCH + HALO + lc];
+        const double* b = s_p + (lane % R) * PITCH + lane / R * R;
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) P[j] = b[j];
+        strip_diff<R, SCHEME>(P, v.hasy ? ks.eh : ks.ek, dh);
+        plane_sync<2>();
+#pragma unroll
+        for (int q = 0; q < R; ++q) s_p[(lane % R) * XPITCH + lane / R * R + q] = dh[q];
+        plane_sync<2>();
+        const double ax = v.hasy ? ks.vh : ks.vk, ay = v.hasy ? ks.vs : 0.0;
+        const double vx = v.negx ? -ax : ax, vy = v.negy ? -ay : ay;
+        const double ncx = -(g.cx() * ax), ncy = -(g.cy() * ay);
+#pragma unroll
+        for (int mc = 0; mc < R; ++mc) {
+            const int mr = v.negy ? R - 1 - mc : mc;
+            const double* sc = st + mr * 64 + lane;
+            const double eta = __builtin_fma(vx, sc[3 * R * 64], vy * sc[4 * R * 64]);
+            double fn = __builtin_fma(omct, fc[mc],
+                                      sc[v.s * R * 64] * feq_poly(eta, sc[5 * R * 64]));
+            fn = __builtin_fma(ncx, s_p[mc * XPITCH + lc], fn);
+            fn = __builtin_fma(ncy, dhy[mc], fn);
+            double* row = g.fout() + v.i * plane + (int64_t)y0 * nx + g.x0;
+            if constexpr (FAST)
+                row_store<NT>(fn, rows_rsrc(row, R * rb), 8u * (unsigned)lane, uniform(mr * rb));
+            else
+                row_store<NT>(fn, rows_rsrc(row + (int64_t)mr * nx, y0 + mr < ny ? 8 * wd : 0),
+                              8u * (unsigned)lane, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    finish(va, dya);
+    finish(vb, dyb);
+    if (hasc) {
+        double z[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) z[q] = 0.0;
+        finish(vc, z);
+    }
+}
+
+
+template <int R, bool NT, bool FAST, int SCHEME, class Grid>
+__device__ __forceinline__ void tile_step_any(const Grid& g, const TileConsts& k, double* lds)
+{
+    if constexpr (tile_waves(R) == 8)
+        tile8_step<R, NT, FAST, SCHEME>(g, k, lds);
+    else
+        tile_step<R, NT, FAST, SCHEME>(g, k, lds);
+}
+
 // Tile g of either kind.
 template <int R, bool NT, int SCHEME, class Grid>
 __device__ __forceinline__ void tile_any(const Grid& g, const TileConsts& k, double* lds)
 {
     if (g.nx() <= TILE_MAX_NX && fast_tile(g.bc(), g.x0, g.y0, TX, R, HALO))
-        tile_step<R, NT, true, SCHEME>(g, k, lds);
+        tile_step_any<R, NT, true, SCHEME>(g, k, lds);
     else
-        tile_step<R, NT, false, SCHEME>(g, k, lds);
+        tile_step_any<R, NT, false, SCHEME>(g, k, lds);
 }
 
 // A launch over one grid: one workgroup per tile, XCD-major over the strip walk

@@ -585,8 +585,12 @@ class Context:
         return out, sums_out
 
     def carries_sums(self):
-        """True when the step variant carries the moment sums (modes 1, 3)."""
-        return lbm_step_variant_info(self.variant)[5] in (1, 3)
+        """True when step_sums carries the moment sums from step to step: with
+        the step variants of modes 1 and 3, and with the whole-tile variants on
+        grids of 2^21 cells or more, where it takes the fast-tile kernel."""
+        info = lbm_step_variant_info(self.variant)
+        tile = info[1] == 18 and info[5] == 0
+        return info[5] in (1, 3) or (tile and self.nx * self.ny >= 1 << 21)
 
     def kinetic_y(self, f):
         out = torch.empty(2, dtype=torch.float64, device=self.device)

@@ -74,12 +74,6 @@ class KHIProblem:
         self._basis = None  # the mode basis of the grid, formed on first use
         if variant is not None:
             self.ctx.variant = variant
-        elif nx * ny >= 1 << 21:
-            # the fast-tile variant, whose sums save the reverse steps their
-            # pass over f (2048^2: 90 of 860 us), also where another forward
-            # step is the faster one alone (1500^2: by 30 us)
-            info = [lbm.lbm_step_variant_info(v) for v in range(lbm.lbm_step_variant_count())]
-            self.ctx.variant = info.index((4, 1, 2, 1, 1, 3))
 
     def weight(self, n):
         return self.dt if self.n0 <= n <= self.n1 else 0.0
@@ -149,7 +143,7 @@ class KHIProblem:
                     f = ctx.step(f, K2)
                     sub[n] = f
             states = [sub.pop(s0)]
-            if lbm.lbm_step_variant_info(ctx.variant)[5] == 3:
+            if ctx.carries_sums() and lbm.lbm_step_variant_info(ctx.variant)[5] != 1:
                 sums = [ctx.sums(states[0])]
                 for _ in range(s0 + 1, s1):
                     f, m = ctx.step_sums(states[-1], sums[-1])

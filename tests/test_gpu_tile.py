@@ -73,6 +73,22 @@ def test_default_variant_and_batches_of_it():
                 assert torch.equal(b.view(out, i), c.step(b.view(f0, i).contiguous(), 5)), (v, i)
 
 
+@pytest.mark.parametrize("shape", [(2051, 1023), (1023, 2049)])
+def test_step_sums_of_a_whole_tile_variant(shape):
+    """On both sides of 2^21 cells, from which on step_sums takes another
+    kernel: the state of step, and the sums of that state, bit for bit."""
+    tile, _ = _variants()
+    nx, ny = shape
+    ctx = lbm.Context(nx, ny, 2e-2, 2.5e-2, 4e-4, 6e-4, (P, P, R, O))
+    assert ctx.variant in tile and ctx.carries_sums() == (nx * ny >= 1 << 21)
+    f = torch.as_tensor(inputs.random_f(nx, ny, seed=5), device="cuda")
+    want = ctx.step(f)
+    for m in (None, ctx.sums(f)):
+        got, sums = ctx.step_sums(f, m)
+        assert torch.equal(got, want)
+        assert torch.equal(sums, ctx.sums(want))
+
+
 def test_very_wide_grid():
     """Past 2^24 cells per row, where every tile takes the boundary path."""
     tile, ref = _variants()
