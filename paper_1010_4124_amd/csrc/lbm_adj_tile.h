@@ -131,16 +131,11 @@ __device__ __forceinline__ void adj_tile_step(const AdjArgs& a, int x0, int y0, 
                 const double* base = (q.lam ? a.lam1 : a.f) + i * plane;
                 return base[q.any ? (int64_t)(y0 + m) * nx + wrap_once(x0 + q.col, nx) : 0];
             } else {
-                int col = 0, kind = CK_NONE, cz = 0, kz = CK_NONE;
+                int col = 0, kind = CK_NONE;
                 const bool in = q.any && y0 + m < ny;
-                if (in) {
-                    x_source_g<false>(b, x0 + q.col, col, kind);
-                    x_source_g<true>(b, x0 + q.col, cz, kz);
-                }
-                if (q.lam) {
-                    col = cz;
-                    kind = kz;
-                }
+                if (in)
+                    x_source_g<false>(b, wrap_near(x0 + q.col, nx, b.bc[XLO], b.bc[XHI]), col, kind);
+                if (q.lam && kind != CK_NORM) kind = CK_NONE;  // (lambda is zero outside)
                 const bool ld = kind == CK_NORM || kind == CK_MIRX;
                 const double* base = (q.lam ? a.lam1 : a.f) + (kind == CK_MIRX ? k.mirx[i] : i) * plane;
                 const double x = base[ld ? (int64_t)(y0 + m) * nx + col : 0];
@@ -149,22 +144,6 @@ __device__ __forceinline__ void adj_tile_step(const AdjArgs& a, int x0, int y0, 
                 return ld ? x : c;
             }
         };
-        // row y of plane i, all lanes alike (ZG: of lambda, zero outside)
-        auto row = [&](auto zg, int i, int y) {
-            constexpr bool ZG = decltype(zg)::value;
-            const double* base = ZG ? a.lam1 : a.f;
-            if constexpr (FAST) {
-                return row_load(rows_rsrc(base + i * plane + (int64_t)y * nx + x0, 512), l8, 0);
-            } else {
-                const RowDesc rd = row_desc_g<ZG>(b, y);
-                const int j = rd.mode == RM_MIRY ? k.miry[i] : i;
-                const bool ld = rd.mode == RM_NORM || rd.mode == RM_MIRY;
-                return row_load(rows_rsrc(base + j * plane + (int64_t)rd.src * nx + x0,
-                                          ld ? 8 * w : 0), l8, 0);
-            }
-        };
-        using T = std::true_type;
-        using F = std::false_type;
         {
             // (waves without such a velocity skip its rows by their range)
             auto nrow = [&](const double* base, int y) {
@@ -210,19 +189,25 @@ __device__ __forceinline__ void adj_tile_step(const AdjArgs& a, int x0, int y0, 
 #pragma unroll
             for (int j = 0; j < LR; ++j) L[j] = row_load(rl, l8, uniform(sl + j * sd));
         } else {
+            const RowSources rf = row_sources<false>(b, a.f, v.iy, k.miry[v.iy], x0, w, [&](int j) {
+                return v.negy ? y0 + R + 3 - j : y0 - 4 + j;
+            }, FR, lane);
+            const RowSources rl = row_sources<true>(b, a.lam1, v.iy, k.miry[v.iy], x0, w, [&](int j) {
+                return v.negy ? y0 + R + 2 - j : y0 - 3 + j;
+            }, LR, lane);
 #pragma unroll
-            for (int j = 0; j < FR; ++j) f[j] = row(F{}, v.iy, v.negy ? y0 + R + 3 - j : y0 - 4 + j);
+            for (int j = 0; j < FR; ++j) f[j] = rf.load(j, l8);
 #pragma unroll
-            for (int j = 0; j < LR; ++j) L[j] = row(T{}, v.iy, v.negy ? y0 + R + 2 - j : y0 - 3 + j);
-        }
-        if constexpr (FAST) rest_rows();
-        if constexpr (!FAST) {  // rows of a fixed-equilibrium side
+            for (int j = 0; j < LR; ++j) L[j] = rl.load(j, l8);
+            if (rf.fixed) {  // rows of a fixed-equilibrium side
 #pragma unroll
-            for (int j = 0; j < FR; ++j) {
-                const RowDesc rd = row_desc_g<false>(b, v.negy ? y0 + R + 3 - j : y0 - 4 + j);
-                if (rd.mode == RM_CONST) f[j] = k.side_eq[rd.side][v.iy];
+                for (int j = 0; j < FR; ++j) {
+                    const bool low = (v.negy ? y0 + R + 3 - j : y0 - 4 + j) < 0;
+                    if (rf.fixed >> j & 1) f[j] = k.side_eq[low ? YLO : YHI][v.iy];
+                }
             }
         }
+        if constexpr (FAST) rest_rows();
         // ---- stage
         if (FAST || lane < w) {
             const int yc = v.ynegx ? 63 - lane : lane;

@@ -161,6 +161,46 @@ __device__ __forceinline__ TileWave tile_wave(int wave)
     return v;
 }
 
+// v around a periodic axis of n, without the division of x_source_g and
+// row_desc_g where the tile and its halo reach less than a period beyond it.
+__device__ __forceinline__ int wrap_near(int v, int n, int lo, int hi)
+{
+    return lo == PERIODIC && hi == PERIODIC && n >= 12 ? wrap_once(v, n) : v;
+}
+
+// Sources of the rows of one plane of a boundary tile, row j in lane j: one
+// evaluation of row_desc_g for all of them (row by row, with all lanes alike,
+// these were most of the instructions of such a tile, which took 4 times the
+// others' time: 400 x 4 6.9 us per step, 6.1 so; 1101 x 605 66.6 and 60.4).
+struct RowSources {
+    unsigned long long at;     // address of the row's first column in the tile
+    int bytes;                 // its length, 0: reads as zero
+    unsigned long long fixed;  // rows of a fixed-equilibrium side (all lanes)
+    __device__ __forceinline__ double load(int j, unsigned v) const
+    {
+        const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)at, j);
+        const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(at >> 32), j);
+        return row_load(rows_rsrc((const double*)((unsigned long long)hi << 32 | lo),
+                                  __builtin_amdgcn_readlane(bytes, j)), v, 0);
+    }
+};
+// Plane i of the grid b's field (im: its mirror partner in y), w columns from
+// x0, rows row(0 .. n-1); ZG: zero outside the domain.
+template <bool ZG, class Row>
+__device__ __forceinline__ RowSources row_sources(const GridBC& b, const double* field, int i,
+                                                  int im, int x0, int w, Row&& row, int n, int lane)
+{
+    const int64_t plane = (int64_t)b.nx * b.ny;
+    const int y = row(min(lane, n - 1));
+    const RowDesc rd = row_desc_g<ZG>(b, wrap_near(y, b.ny, b.bc[YLO], b.bc[YHI]));
+    const double* src = rd.mode == RM_OUT
+                            ? (rd.side == YLO ? b.gb[YLO] : b.gb[YHI]) + (int64_t)i * b.nx
+                            : field + (rd.mode == RM_MIRY ? im : i) * plane + (int64_t)rd.src * b.nx;
+    return RowSources{(unsigned long long)(src + x0),
+                      rd.mode == RM_CONST || rd.mode == RM_NONE ? 0 : 8 * w,
+                      __ballot(lane < n && rd.mode == RM_CONST)};
+}
+
 // Halo lanes (lane < 5 R): row lane / 5 (canonical) and one of five columns,
 // counted from the tile's first cell: -3, -2, -1, w, w+1 for v_x > 0 (the
 // reach of its upwind stencils), the mirrored w+2, w+1, w, -1, -2 for v_x < 0.
@@ -224,7 +264,7 @@ __device__ __forceinline__ void vel_load(const Grid& g, const TileConsts& k, con
         // halo values of the rows inside the domain
         int col = 0, kind = CK_NONE;
         const int hy = y0 + hm;
-        if (hl && hy < ny) x_source_g<false>(b, hx, col, kind);
+        if (hl && hy < ny) x_source_g<false>(b, wrap_near(hx, nx, b.bc[XLO], b.bc[XHI]), col, kind);
         const bool out = kind == CK_OUTLO || kind == CK_OUTHI;
         const int64_t off = out ? (int64_t)v.i * ny + hy
                                 : (kind == CK_MIRX ? ix : v.i) * plane + (int64_t)hy * nx + col;
@@ -233,22 +273,19 @@ __device__ __forceinline__ void vel_load(const Grid& g, const TileConsts& k, con
         const double x = base[ld ? off : 0];
         const double c = kind == CK_CXLO ? g.side_eq(k, XLO, v.i) : g.side_eq(k, XHI, v.i);
         h = ld ? x : kind == CK_NONE ? 0.0 : c;
-        auto row = [&](int j) {  // (a row's source is the same for all lanes)
-            const RowDesc rd = row_desc_g<false>(b, v.negy ? y0 + R + 2 - j : y0 - HALO + j);
-            const double* src = fin + (rd.mode == RM_MIRY ? im : v.i) * plane +
-                                (int64_t)rd.src * nx;
-            if (rd.mode == RM_OUT)
-                src = (rd.side == YLO ? b.gb[YLO] : b.gb[YHI]) + (int64_t)v.i * nx;
-            const bool l = rd.mode != RM_CONST && rd.mode != RM_NONE;
-            return row_load(rows_rsrc(src + x0, l ? 8 * w : 0), l8, 0);
-        };
         if (v.hasy) {
+            const RowSources rs = row_sources<false>(b, fin, v.i, im, x0, w, [&](int j) {
+                return v.negy ? y0 + R + 2 - j : y0 - HALO + j;
+            }, ROWS, lane);
 #pragma unroll
-            for (int j = 0; j < ROWS; ++j) p[j] = row(j);
+            for (int j = 0; j < ROWS; ++j) p[j] = rs.load(j, l8);
+            if (rs.fixed) {  // rows of a fixed-equilibrium side
 #pragma unroll
-            for (int j = 0; j < ROWS; ++j) {  // rows of a fixed-equilibrium side
-                const RowDesc rd = row_desc_g<false>(b, v.negy ? y0 + R + 2 - j : y0 - HALO + j);
-                if (rd.mode == RM_CONST) p[j] = g.side_eq(k, rd.side, v.i);
+                for (int j = 0; j < ROWS; ++j) {
+                    const bool low = (v.negy ? y0 + R + 2 - j : y0 - HALO + j) < 0;
+                    if (rs.fixed >> j & 1)
+                        p[j] = low ? g.side_eq(k, YLO, v.i) : g.side_eq(k, YHI, v.i);
+                }
             }
         } else {
 #pragma unroll
