@@ -579,7 +579,7 @@ def summarize_batch(trace, log_path, commands):
         f"# Batched step, 64-instance shear-layer sweep ({cells} cells): kernel durations",
         "",
         "The sweep's instances (seed 2024) have sizes drawn from {128, 192, 256, 384, 512}^2; one "
-        "launch of lbmd::k_step_batch advances all of them by one step, and "
+        "launch of the batched step kernel advances all of them by one step, and "
         "lbmd::k_reduce_batch turns the per-tile partials into the 64 energy-log entries. The "
         f"step variant is fixed to {tuple(v)}, the one the bench's tuner picks for this sweep "
         "(the tuner's own short trials run perturbed under the tracer), with one workgroup per "

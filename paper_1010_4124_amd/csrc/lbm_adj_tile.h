@@ -21,7 +21,7 @@
 // operations each: ~10 us of a tile's ~18) and, with one workgroup per CU
 // (142 KB of LDS, 168 registers), the phases that do not overlap. Measured per
 // reverse step, against the state pass and one workgroup per tile and velocity:
-// 128^2 21 us (27), 256^2 23 us (40), 600 x 200 42 us (69).
+// 128^2 19 us (27), 256^2 21 us (40), 600 x 200 37 us (68).
 #pragma once
 
 #include "lbm_tile.h"

@@ -445,14 +445,14 @@ int lbm_get_step_variant(lbm_ctx* c, int32_t* v)
 // from the numbers of 64 x 1, 64 x 2 and 64 x 4 tiles (over all instances of a
 // batch), as measured on MI355X (microseconds per step, shear layers):
 //  - A whole-tile step takes the latency of one tile while all its workgroups
-//    are resident at once, less for lower tiles: 128^2 takes 7.5 with R = 1
-//    (256 tiles), 8.3 with R = 2, 11.5 with R = 4 (state pass and plane kernel:
-//    12.2); 256^2 14.2, 10.9 (512 tiles), 12.4 (17.0).
-//  - Beyond that R = 4, which reads the fewest halo rows: 512^2 25.9 against
-//    30.2 with R = 2 and 37.0 for state pass and plane kernel. Non-temporal
+//    are resident at once, less for lower tiles: 128^2 takes 6.0 with R = 1
+//    (256 tiles), 6.7 with R = 2, 10.1 with R = 4 (state pass and plane kernel:
+//    12.2); 256^2 12.9, 10.4 (512 tiles), 10.5 (17.0).
+//  - Beyond that R = 4, which reads the fewest halo rows: 512^2 25.2 against
+//    28.7 with R = 2 and 37.0 for state pass and plane kernel. Non-temporal
 //    stores from 2^20 cells on, where two states exceed the 256 MB cache:
 //    2048^2 309 against 340; below, the next step finds the state there
-//    (1101 x 605 69 against 62, four outflow grids of 600 x 200 62 against 53).
+//    (1101 x 605 65 against 60, four outflow grids of 600 x 200 59 against 54).
 //  - The fast-tile kernel with its carried sums moves 400 B per cell instead of
 //    310, in rounds of 2048 tiles and with band tiles of 85 us at the grid's
 //    edge: 1024^2 97 against 88, 1448^2 230 against 180, 3000 x 1000 279 against
@@ -632,16 +632,19 @@ int lbm_tune_step(lbm_ctx* c, const double* f_in, double* f_tmp, int32_t nsteps,
 // Default reverse-step variant. Measured on MI355X (shear layers, us a step,
 // whole-tile kernel / marching kernel with chunks of 32 rows / of 64 rows / one
 // velocity per 64 x 4 tile after a state pass):
-//   128^2 21 / 28 / - / 27, 256^2 23 / 33 / - / 40, 600 x 200 42 / 51 / 56 / 69,
-//   384^2 55 / 51 / 58 / 61, 512^2 73 / 72 / 81 / 85, 1101 x 605 200 / 169 / 174 / 272,
-//   1024^2 293 / 221 / 229 / 293, 1448^2 608 / 476 / 478 / -, 2048^2 1115 / 894 / 860 / -.
+//   128^2 19 / 28 / - / 27, 256^2 21 / 34 / - / 40, 600 x 200 37 / 53 / 56 / 68,
+//   384^2 51 / 50 / 58 / 60, 512^2 70 / 72 / 81 / 85, 1101 x 605 193 / 168 / 174 / 271,
+//   1024^2 283 / 220 / 230 / 289, 1101^2 364 / 298 / 306, 1200 x 1050 363 / 292 / 289,
+//   800 x 1900 438 / 365 / 358, 1448^2 590 / 484 / 481, 2048^2 1105 / 871 / 865.
 // The whole-tile kernel runs one workgroup per CU, in rounds of 256 tiles of
 // about 18 us, against the marching kernel's chain of a state pass and a long
-// march: it wins while its tiles take at most two rounds.
+// march: it wins while its tiles take at most two rounds. Chunks of 32 rows
+// read more halo rows but give twice the wavefronts, of use below 1.2 x 2^20
+// cells.
 int lbmi_default_adj_variant(int nx, int ny)
 {
     const int64_t tiles = ((int64_t)nx + 63) / 64 * (((int64_t)ny + 3) / 4);
-    const bool big = (int64_t)nx * ny >= 3 * (1ll << 20) / 2;
+    const bool big = (int64_t)nx * ny >= 6 * (1ll << 20) / 5;
     const int tile_v[4] = {4, 18, 3, 0}, march_v[4] = {big ? 64 : 32, 18, 2, 2};
     const int* want = tiles <= 512 ? tile_v : march_v;
     for (int v = 0; v < adj_variant_count(); ++v) {

@@ -6,9 +6,9 @@
 // images for v < 0) is c (first order) or c + (c - b)/2 (second order), times v.
 //
 // Bound by the latency of a tile on small grids (400 x 4 shock tube, second
-// order: 7.2 us a step, against 54 with one thread per cell that took the 18
+// order: 6.1 us a step, against 54 with one thread per cell that took the 18
 // velocities in turn in 7 workgroups) and by moving the planes on large ones
-// (2048^2: 296 us, 4.3 TB/s of the 304 B per cell, against 1405).
+// (2048^2: 275 us, 4.6 TB/s of the 304 B per cell, against 1405).
 #include "lbm_device.h"
 #include "lbm_internal.h"
 #include "lbm_stage.h"

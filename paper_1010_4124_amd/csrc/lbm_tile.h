@@ -34,8 +34,8 @@
 // the three of tile8_step (R = 4) VALU is busy 69% of the time at 2048^2, with
 // HBM traffic of 310 B per cell of the 304 it cannot do without (the fast-tile
 // kernel: 408). Measured per step, against the state pass and plane kernel it
-// replaces: 400 x 4 6.9 us (12.6), 256^2 10.8 (17.0), 512^2 26.4 (37.0),
-// 1101 x 605 63 (101), four outflow grids of 600 x 200 in a batch 53 (76).
+// replaces: 400 x 4 6.1 us (12.6), 256^2 10.4 (17.0), 512^2 25.2 (37.0),
+// 1101 x 605 60 (101), four outflow grids of 600 x 200 in a batch 54 (76).
 #pragma once
 
 #include "lbm_device.h"
