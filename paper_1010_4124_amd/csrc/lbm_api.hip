@@ -457,9 +457,11 @@ int lbm_get_step_variant(lbm_ctx* c, int32_t* v)
 //    310, in rounds of 2048 tiles and with band tiles of 85 us at the grid's
 //    edge: 1024^2 97 against 88, 1448^2 230 against 180, 3000 x 1000 279 against
 //    247, a 64-instance sweep of 5.3 M cells 468-490 against 449-456. On large
-//    single grids of whole tile columns, which leave it little of either, it is
-//    level and then ahead: 2048^2 (8 rounds) 317 against 324, 4096^2 1180
-//    against 1250.
+//    single grids of whole tile columns and nearly full rounds, which leave it
+//    little of either, it is level and then ahead: 3072 x 1024 (6 rounds) 262
+//    against 259, 2048 x 1536 (6) 242 against 248, 2560 x 1600 (7.8) both 331,
+//    2048^2 (8) 317 against 324, 4096^2 1180 against 1250; not 4096 x 960 (7.5)
+//    325 against 312, 1536 x 1408 (4.1) 177 against 176.
 int lbmi_tile_rows(int64_t t1, int64_t t2)
 {
     constexpr int64_t RESIDENT = 512;
@@ -500,7 +502,7 @@ int lbmi_default_variant(int nx, int ny)
     constexpr int64_t ROUND = 2048;
     const int64_t tx = ((int64_t)nx + 63) / 64, t4 = tx * (((int64_t)ny + 3) / 4);
     const int64_t rounds = (t4 + ROUND - 1) / ROUND;
-    if (nx % 64 == 0 && t4 >= 8 * ROUND && 10 * t4 >= 9 * ROUND * rounds)
+    if (nx % 64 == 0 && t4 >= 6 * ROUND && 100 * t4 >= 97 * ROUND * rounds)
         return variant_index({4, 1, 2, 1, 1, 3});
     return lbmi_default_variant_tiles(tx * ny, tx * (((int64_t)ny + 1) / 2), t4);
 }
