@@ -468,6 +468,8 @@ int lbmi_tile_rows(int64_t t1, int64_t t2)
     return t1 <= RESIDENT ? 1 : t2 <= RESIDENT ? 2 : 4;
 }
 
+int64_t lbmi_launch_span(int threads) { return ((1ll << 32) - 1) / threads & ~7ll; }
+
 static int variant_index(const int (&want)[6])
 {
     for (int v = 0; v < step_variant_count(); ++v) {

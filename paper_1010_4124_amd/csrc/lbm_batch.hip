@@ -62,6 +62,7 @@ struct BatchArgs {
     const double* __restrict__ m_in;       // carried moment sums (M variants)
     double* __restrict__ m_out;
     int nwork, per_xcd, slots;
+    int first;  // workgroup number of a whole-tile launch's first (launch_spans)
     Consts k;
 };
 
@@ -157,7 +158,7 @@ void k_step_batch_tile(BatchArgs a, TileConsts k)
 {
     __shared__ double lds[TileWg<R>::LDS];
 
-    const int b = blockIdx.x;
+    const int b = a.first + (int)blockIdx.x;
     const int work = (b & 7) * a.per_xcd + (b >> 3);
     if (work >= a.nwork) return;
     const int2 it = a.work[work];
@@ -422,11 +423,14 @@ hipError_t launch_batch_step(lbm_batch* b, const double* src, double* dst, bool 
     a.nwork = b->nwork;
     a.per_xcd = (b->nwork + 7) / 8;
     a.slots = b->slots > 0 ? std::min(b->slots, a.per_xcd) : a.per_xcd;
+    a.first = 0;
     a.k = b->k;
     if (V.M == PH_TILE) {
-        hipLaunchKernelGGL(V.tile, dim3(8 * a.per_xcd), dim3(64 * tile_waves(V.R)), 0, st, a,
-                           tile_consts(b->k));
-        return hipGetLastError();
+        const int threads = 64 * tile_waves(V.R);
+        return launch_spans(8ll * a.per_xcd, threads, [&](int first, unsigned count) {
+            a.first = first;
+            hipLaunchKernelGGL(V.tile, dim3(count), dim3(threads), 0, st, a, tile_consts(b->k));
+        });
     }
     hipLaunchKernelGGL(V.kernel, dim3(8 * a.slots), dim3(64 * (V.M == PH_CARRY ? V.G : 1)), 0, st,
                        a);

@@ -454,9 +454,7 @@ hipError_t launch_step(int variant, const double* fin, double* fout, const Const
         return hipGetLastError();
     }
     if (V.M == PH_TILE) {
-        const TileArgs t = tile_args(a.s, k, ke_part, V.R);
-        hipLaunchKernelGGL(V.tile, dim3(8 * t.per_xcd), dim3(64 * tile_waves(V.R)), 0, st, t);
-        return hipGetLastError();
+        return launch_tiles(V.tile, tile_args(a.s, k, ke_part, V.R), V.R, st);
     }
     a.nwork = a.s.tiles_x * a.tiles_y * (V.M == PH_CARRY ? 1 : V.G);
     a.per_xcd = (a.nwork + 7) / 8;

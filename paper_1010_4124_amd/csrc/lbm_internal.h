@@ -33,7 +33,29 @@ int lbmi_tile_rows(int64_t t1, int64_t t2);  // rows of a whole-tile step's tile
 int lbmi_default_adj_variant(int nx, int ny);
 void lbmi_set_error(const char* msg);
 
+extern "C" {
+// Workgroups of `threads` threads that one launch may have, a multiple of 8: a
+// grid dimension of 2^32 work-items or more is refused.
+int64_t lbmi_launch_span(int threads);
+}
+
 namespace lbmd {
+// launch(first, count) over `blocks` workgroups of `threads` threads, in as many
+// launches as their number takes (one below 2^32 threads). The kernel's workgroup
+// number is first + blockIdx.x; first is a multiple of 8, so workgroups keep
+// their XCD.
+template <class Launch>
+hipError_t launch_spans(int64_t blocks, int threads, Launch&& launch)
+{
+    const int64_t span = lbmi_launch_span(threads);
+    for (int64_t first = 0; first < blocks; first += span) {
+        launch((int)first, (unsigned)(blocks - first < span ? blocks - first : span));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 int step_variant_count();
 int step_variant_desc(int v, int info[6]);
 int step_ntiles(int variant, int nx, int ny);

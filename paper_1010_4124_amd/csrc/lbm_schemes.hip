@@ -45,10 +45,7 @@ hipError_t launch_step_lo(int scheme, int R, const double* fin, double* fout, co
     void (*const kernels[3][2])(TileArgs) = {{k_step_lo<1, 1>, k_step_lo<1, 2>},
                                              {k_step_lo<2, 1>, k_step_lo<2, 2>},
                                              {k_step_lo<4, 1>, k_step_lo<4, 2>}};
-    const TileArgs t = tile_args(s, k, ke_part, R);
-    hipLaunchKernelGGL(kernels[R >> 1][scheme == 1 ? 0 : 1], dim3(8 * t.per_xcd),
-                       dim3(64 * tile_waves(R)), 0, st, t);
-    return hipGetLastError();
+    return launch_tiles(kernels[R >> 1][scheme == 1 ? 0 : 1], tile_args(s, k, ke_part, R), R, st);
 }
 
 }  // namespace lbmd

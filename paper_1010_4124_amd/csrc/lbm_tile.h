@@ -39,6 +39,7 @@
 #pragma once
 
 #include "lbm_device.h"
+#include "lbm_internal.h"
 #include "lbm_stage.h"
 #include "lbm_step.h"
 
@@ -704,6 +705,7 @@ struct TileArgs {
     StepGrid s;
     double* __restrict__ ke_part;  // [ntiles][2] or null
     int tiles_y, nwork, per_xcd;
+    int first;  // workgroup number of the launch's first (launch_spans)
     TileConsts k;
 };
 
@@ -736,15 +738,26 @@ inline TileArgs tile_args(const StepGrid& s, const Consts& k, double* ke_part, i
     t.tiles_y = (s.ny + R - 1) / R;
     t.nwork = t.s.tiles_x * t.tiles_y;
     t.per_xcd = (t.nwork + 7) / 8;
+    t.first = 0;
     t.k = tile_consts(k);
     return t;
+}
+
+// Launches `kernel` over all tiles of t in tiles of R rows.
+inline hipError_t launch_tiles(void (*kernel)(TileArgs), TileArgs t, int R, hipStream_t st)
+{
+    const int threads = 64 * tile_waves(R);
+    return launch_spans(8ll * t.per_xcd, threads, [&](int first, unsigned count) {
+        t.first = first;
+        hipLaunchKernelGGL(kernel, dim3(count), dim3(threads), 0, st, t);
+    });
 }
 
 // Workgroup blockIdx.x of such a launch.
 template <int R, bool NT, int SCHEME>
 __device__ __forceinline__ void tile_block(const TileArgs& a, double* lds)
 {
-    const int b = blockIdx.x;
+    const int b = a.first + (int)blockIdx.x;
     const int work = (b & 7) * a.per_xcd + (b >> 3);
     if (work >= a.nwork) return;
     const TileXY t = strip_walk_xy(work, a.s.tiles_x, a.tiles_y);
