@@ -254,10 +254,9 @@ int lbm_step(lbm_ctx* c, const double* f_in, double* f_out, int32_t nsteps, doub
     const lbm_params& p = c->p;
     const double cx = p.dt / p.dx, cy = p.dt / p.dy, ct = p.dt / p.tau;
     if (p.scheme != LBM_SCHEME_WENO5) {
-        // comparison schemes: one whole-tile kernel per step
-        const int64_t tx = ((int64_t)p.nx + 63) / 64;
-        const int R = lbmi_tile_rows(tx * p.ny, tx * ((p.ny + 1) / 2));
-        const int nparts = (int)(tx * ((p.ny + R - 1) / R));
+        // comparison schemes: one kernel per step
+        const int R = lbmi_upwind_rows(p.scheme, p.nx, p.ny);
+        const int nparts = R ? (p.nx + 63) / 64 * ((p.ny + R - 1) / R) : (int)((n + 255) / 256);
         for (int s = 0; s < nsteps; ++s) {
             const double* src = s == 0 ? f_in : (((nsteps - s) % 2 == 0) ? f_out : c->scratch);
             double* dst = ((nsteps - 1 - s) % 2 == 0) ? f_out : c->scratch;
@@ -466,6 +465,22 @@ int lbmi_tile_rows(int64_t t1, int64_t t2)
 {
     constexpr int64_t RESIDENT = 512;
     return t1 <= RESIDENT ? 1 : t2 <= RESIDENT ? 2 : 4;
+}
+
+// Upwind schemes: whole tiles, or one thread per cell where that takes less
+// time, as on tall grids of a few columns. Nanoseconds per step as measured
+// (tiles of 4 rows where not memory-bound; per cell, first / second order:
+// 28 / 40 us at least): 1 x 480000 first order 110 us per cell and 1212 in
+// tiles, 8 x 480000 781 and 1262, 12 x 480000 1125 and 1226, 14 x 480000 1283
+// and 1245; 1 x 8000 27 and 24, 1 x 16000 27 and 44; second order 4 x 480000 686
+// and 1290, 7 x 480000 1143 and 1302, 8 x 480000 1357 and 1304, 6 x 16000 50 and 46.
+int lbmi_upwind_rows(int scheme, int nx, int ny)
+{
+    const int64_t tx = ((int64_t)nx + 63) / 64, n = (int64_t)nx * ny;
+    const double tiles = 3e3 + 10.5 * (double)(tx * (((int64_t)ny + 3) / 4));
+    const double cells = scheme == LBM_SCHEME_UPWIND1 ? std::max(28e3, 12e3 + 0.20 * (double)n)
+                                                      : std::max(40e3, 16e3 + 0.35 * (double)n);
+    return cells < tiles ? 0 : lbmi_tile_rows(tx * ny, tx * (((int64_t)ny + 1) / 2));
 }
 
 int64_t lbmi_launch_span(int threads) { return ((1ll << 32) - 1) / threads & ~7ll; }

@@ -37,6 +37,7 @@ extern "C" {
 // Workgroups of `threads` threads that one launch may have, a multiple of 8: a
 // grid dimension of 2^32 work-items or more is refused.
 int64_t lbmi_launch_span(int threads);
+int lbmi_upwind_rows(int scheme, int nx, int ny);  // R of launch_step_lo
 }
 
 namespace lbmd {
@@ -67,7 +68,7 @@ hipError_t launch_step(int variant, const double* fin, double* fout, const Const
 // (launch_sums' layout) before the step reads them; the fast-tile kernel
 // forms them in its tiles and writes only those of the band tiles to m_in
 // one step of an upwind scheme in tiles of 64 x R cells (R = 1, 2 or 4), energy
-// partials per tile
+// partials per tile, or (R = 0) by one thread per cell, partials per 256 cells
 hipError_t launch_step_lo(int scheme, int R, const double* fin, double* fout, const Consts& k,
                           double* ke_part, int nx, int ny, const int bc[4], double cx, double cy, double ct, int ke_axis,
                           const double* const gb[4], hipStream_t st);
