@@ -133,7 +133,7 @@ int lbm_create(const lbm_params* p, lbm_ctx** out)
     }
     lbmi_fill_consts(p, &c->k);
     const size_t n = (size_t)p->nx * p->ny;
-    c->variant = lbmi_default_variant(p->nx, p->ny);
+    c->variant = lbmi_default_variant(p->nx, p->ny, p->bc[XLO]);
     c->adj_variant = lbmi_default_adj_variant(p->nx, p->ny);
     // energy partials: room for one step of any variant, and for KE_ROWS steps,
     // reduced by one launch, of those with tiles of two rows or more (fewer
@@ -453,14 +453,17 @@ int lbm_get_step_variant(lbm_ctx* c, int32_t* v)
 //    2048^2 309 against 340; below, the next step finds the state there
 //    (1101 x 605 65 against 60, four outflow grids of 600 x 200 59 against 54).
 //  - The fast-tile kernel with its carried sums moves 400 B per cell instead of
-//    310, in rounds of 2048 tiles and with band tiles of 85 us at the grid's
-//    edge: 1024^2 97 against 88, 1448^2 230 against 180, 3000 x 1000 279 against
-//    247, a 64-instance sweep of 5.3 M cells 468-490 against 449-456. On large
-//    single grids of whole tile columns and nearly full rounds, which leave it
-//    little of either, it is level and then ahead: 3072 x 1024 (6 rounds) 262
-//    against 259, 2048 x 1536 (6) 242 against 248, 2560 x 1600 (7.8) both 331,
-//    2048^2 (8) 317 against 324, 4096^2 1180 against 1250; not 4096 x 960 (7.5)
-//    325 against 312, 1536 x 1408 (4.1) 177 against 176.
+//    310, in rounds of 2048 tiles, and takes some four times as long for a band
+//    tile (one at the grid's edge). On single grids from 4 rounds on it is 2 to
+//    7% ahead where at most one tile in a hundred is a band tile, which takes
+//    an x axis that is periodic and, on all but very large grids, whole tile
+//    columns (fast / whole tiles: 2048 x 1024 183 / 190, 2048 x 1536 270 / 284,
+//    2048^2 356 / 375, 4096^2 1400 / 1500; 0.7% band tiles, 6144 x 1100: 597 / 607),
+//    and behind with more (1.2 and 1.3%, 8200 x 2000 and 6000 x 3000: 1510 / 1487
+//    and 1653 / 1641; 3.1%, 8192 x 256: 222 / 207; 2050^2 466 / 392; a 2048^2 box
+//    552 / 398) and on fewer rounds (1024^2 106 / 97; 1536 x 1024, 3 rounds, 141 / 145).
+//    In a batch it is level at best: four grids of 2048^2 1454 / 1462, two 748 / 732,
+//    a 64-instance sweep of 5.3 M cells 468-490 / 449-456.
 int lbmi_tile_rows(int64_t t1, int64_t t2)
 {
     constexpr int64_t RESIDENT = 512;
@@ -514,12 +517,11 @@ int lbmi_sums_variant(int v, int64_t cells)
     return tile && cells >= (1ll << 21) ? variant_index({4, 1, 2, 1, 1, 3}) : v;
 }
 
-int lbmi_default_variant(int nx, int ny)
+int lbmi_default_variant(int nx, int ny, int bc_xlo)
 {
     constexpr int64_t ROUND = 2048;
     const int64_t tx = ((int64_t)nx + 63) / 64, t4 = tx * (((int64_t)ny + 3) / 4);
-    const int64_t rounds = (t4 + ROUND - 1) / ROUND;
-    if (nx % 64 == 0 && t4 >= 6 * ROUND && 100 * t4 >= 97 * ROUND * rounds)
+    if (t4 >= 4 * ROUND && 100 * fast_band_tiles(nx, ny, bc_xlo, 4) <= t4)
         return variant_index({4, 1, 2, 1, 1, 3});
     return lbmi_default_variant_tiles(tx * ny, tx * (((int64_t)ny + 1) / 2), t4);
 }

@@ -398,6 +398,11 @@ int step_ntiles(int variant, int nx, int ny)
     return ((nx + TX - 1) / TX) * ((ny + V.R - 1) / V.R);
 }
 
+int64_t fast_band_tiles(int nx, int ny, int bc_xlo, int R)
+{
+    return band_count(fast_rect(nx, ny, bc_xlo, R), (nx + TX - 1) / TX, (ny + R - 1) / R);
+}
+
 hipError_t launch_step(int variant, const double* fin, double* fout, const Consts& k,
                        double* ke_part, int nx, int ny, const int bc[4], double cx, double cy,
                        double ct, int ke_axis, const double* const gb[4], const double* m_in,

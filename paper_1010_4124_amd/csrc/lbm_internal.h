@@ -26,7 +26,6 @@ struct lbm_ctx {
 
 int lbmi_validate(const lbm_params* p);
 void lbmi_fill_consts(const lbm_params* p, lbmd::Consts* h);
-int lbmi_default_variant(int nx, int ny);
 int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4);
 int lbmi_sums_variant(int v, int64_t cells);  // the variant lbm_step_sums takes for v
 int lbmi_tile_rows(int64_t t1, int64_t t2);  // rows of a whole-tile step's tiles
@@ -38,6 +37,7 @@ extern "C" {
 // grid dimension of 2^32 work-items or more is refused.
 int64_t lbmi_launch_span(int threads);
 int lbmi_upwind_rows(int scheme, int nx, int ny);  // R of launch_step_lo
+int lbmi_default_variant(int nx, int ny, int bc_xlo);
 }
 
 namespace lbmd {
@@ -60,6 +60,7 @@ hipError_t launch_spans(int64_t blocks, int threads, Launch&& launch)
 int step_variant_count();
 int step_variant_desc(int v, int info[6]);
 int step_ntiles(int variant, int nx, int ny);
+int64_t fast_band_tiles(int nx, int ny, int bc_xlo, int R);  // the fast-tile kernel's band tiles
 hipError_t launch_step(int variant, const double* fin, double* fout, const Consts& k,
                        double* ke_part, int nx, int ny, const int bc[4], double cx, double cy,
                        double ct, int ke_axis, const double* const gb[4], const double* m_in,
