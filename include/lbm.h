@@ -252,8 +252,7 @@ int lbm_sep_project(lbm_ctx* ctx, const double* g, const double* A, int32_t M, c
  * a tile obtains its moments (Eq. (10)):
  *   0  every (tile, group) workgroup sums the 19 planes of f^n itself; with
  *      G = 18 one workgroup of 12 wavefronts takes all velocities of a tile,
- *      each plane read once (a batch launches one workgroup per work item
- *      whatever its slots_per_xcd);
+ *      each plane read once;
  *   1  the sums rho, j, E are carried from each step to the next (a call
  *      first forms them from f_in) and the G groups are the waves of one
  *      workgroup;

@@ -152,21 +152,42 @@ struct TileOfBatch {
     }
 };
 
+// One work item.
 template <int R, bool NT>
-__global__ __launch_bounds__((64 * tile_waves(R))) __attribute__((amdgpu_waves_per_eu(6)))
-void k_step_batch_tile(BatchArgs a, TileConsts k)
+__device__ __forceinline__ void batch_tile(const BatchArgs& a, const TileConsts& k, int work,
+                                           double* lds)
 {
-    __shared__ double lds[TileWg<R>::LDS];
-
-    const int b = a.first + (int)blockIdx.x;
-    const int work = (b & 7) * a.per_xcd + (b >> 3);
-    if (work >= a.nwork) return;
     const int2 it = a.work[work];
     ConstInst* d = (ConstInst*)(a.inst + it.x);
     const int ty = it.y / d->tiles_x, tx = it.y - ty * d->tiles_x;
     const TileOfBatch g{a, d, tx * TX, ty * R,
                         a.ke_part ? a.ke_part + 2 * ((int64_t)d->ke_off + it.y) : nullptr};
     tile_any<R, NT, 0>(g, k, lds);
+}
+
+// LOOP: a persistent grid of 8 a.slots workgroups (slots_per_xcd > 0), each over
+// its XCD's band of the work list, for callers that limit the workgroups (a
+// tile's loads wait behind the last one's stores: a 64-instance sweep of 5.3 M
+// cells takes 527 us per step with 3072 workgroups, 760 with 256); else one
+// workgroup per work item (472).
+template <int R, bool NT, bool LOOP>
+__global__ __launch_bounds__((64 * tile_waves(R))) __attribute__((amdgpu_waves_per_eu(6)))
+void k_step_batch_tile(BatchArgs a, TileConsts k)
+{
+    __shared__ double lds[TileWg<R>::LDS];
+
+    const int b = a.first + (int)blockIdx.x;
+    const int lo = (b & 7) * a.per_xcd;
+    if constexpr (LOOP) {
+        const int hi = min(lo + a.per_xcd, a.nwork);
+        for (int w = lo + (b >> 3); w < hi; w += a.slots) {
+            batch_tile<R, NT>(a, k, w, lds);
+            __syncthreads();  // (the tile's waves have read its planes)
+        }
+    } else {
+        if (lo + (b >> 3) >= a.nwork) return;
+        batch_tile<R, NT>(a, k, lo + (b >> 3), lds);
+    }
 }
 
 // Per-instance reduction of the tile partials: block i writes
@@ -240,7 +261,7 @@ __global__ __launch_bounds__(256) void k_reduce_batch(const double* __restrict__
 struct BatchVariant {
     int R, G, M;
     void (*kernel)(BatchArgs);
-    void (*tile)(BatchArgs, TileConsts);
+    void (*tile[2])(BatchArgs, TileConsts);  // one workgroup per item, persistent grid
     // work items per tile: the velocity groups, unless they share a workgroup
     int items() const { return M == PH_CARRY || M == PH_TILE ? 1 : G; }
 };
@@ -248,11 +269,13 @@ template <int R, int G, int WB, int D, bool NT, int M>
 struct BatchKernel {
     static constexpr void (*fn)(BatchArgs) = k_step_batch<R, G, WB, D, NT, M>;
     static constexpr void (*tile)(BatchArgs, TileConsts) = nullptr;
+    static constexpr void (*loop)(BatchArgs, TileConsts) = nullptr;
 };
 template <int R, int G, int WB, int D, bool NT>
 struct BatchKernel<R, G, WB, D, NT, PH_TILE> {
     static constexpr void (*fn)(BatchArgs) = nullptr;
-    static constexpr void (*tile)(BatchArgs, TileConsts) = k_step_batch_tile<R, NT>;
+    static constexpr void (*tile)(BatchArgs, TileConsts) = k_step_batch_tile<R, NT, false>;
+    static constexpr void (*loop)(BatchArgs, TileConsts) = k_step_batch_tile<R, NT, true>;
 };
 // The batched kernel keeps an instance descriptor live as well and takes the
 // variant's own batch wave target WB, chosen so that it does not spill. The
@@ -260,7 +283,7 @@ struct BatchKernel<R, G, WB, D, NT, PH_TILE> {
 // same work items, sums and buffers.
 #define LBM_BATCH_VARIANT(R, G, W, D, NT, M, WB) \
     {R, G, (M == PH_FAST ? PH_CARRY : M), BatchKernel<R, G, WB, D, NT, M>::fn,                   \
-     BatchKernel<R, G, WB, D, NT, M>::tile},
+     {BatchKernel<R, G, WB, D, NT, M>::tile, BatchKernel<R, G, WB, D, NT, M>::loop}},
 static const BatchVariant kBatchVariants[] = {LBM_STEP_VARIANTS(LBM_BATCH_VARIANT)};
 #undef LBM_BATCH_VARIANT
 
@@ -427,9 +450,10 @@ hipError_t launch_batch_step(lbm_batch* b, const double* src, double* dst, bool 
     a.k = b->k;
     if (V.M == PH_TILE) {
         const int threads = 64 * tile_waves(V.R);
-        return launch_spans(8ll * a.per_xcd, threads, [&](int first, unsigned count) {
+        const auto kernel = V.tile[a.slots < a.per_xcd ? 1 : 0];
+        return launch_spans(8ll * a.slots, threads, [&](int first, unsigned count) {
             a.first = first;
-            hipLaunchKernelGGL(V.tile, dim3(count), dim3(threads), 0, st, a, tile_consts(b->k));
+            hipLaunchKernelGGL(kernel, dim3(count), dim3(threads), 0, st, a, tile_consts(b->k));
         });
     }
     hipLaunchKernelGGL(V.kernel, dim3(8 * a.slots), dim3(64 * (V.M == PH_CARRY ? V.G : 1)), 0, st,
