@@ -6,10 +6,12 @@ winner per device and problem shape in a JSON file, and reapplies it.
 
 Cache file: $LBM_TUNE_CACHE, else ~/.cache/lbm_hip/tune.json. A key names
 the device, the kind of problem (single grid or batch), its shape and
-boundary rules; a batch key covers every instance's shape.
+boundary rules; a batch key covers every instance's shape. An entry holds for
+the library that it was timed with: the variants it offers and the file itself.
 """
 from __future__ import annotations
 
+import functools
 import hashlib
 import json
 import os
@@ -49,6 +51,32 @@ def _device():
     return torch.cuda.get_device_name(torch.cuda.current_device()).replace("|", "/")
 
 
+@functools.lru_cache(maxsize=None)
+def library_signature():
+    """Names the kernels that an entry's times are of."""
+    info = ([lbm.lbm_step_variant_info(v) for v in range(lbm.lbm_step_variant_count())],
+            [lbm.lbm_adjoint_variant_info(v) for v in range(lbm.lbm_adjoint_variant_count())])
+    h = hashlib.sha1(repr(info).encode())
+    with open(lbm.LIB_PATH, "rb") as fh:
+        h.update(fh.read())
+    return h.hexdigest()[:16]
+
+
+def _keep(key, rec):
+    db = _load()
+    db[key] = dict(rec, library=library_signature())
+    _store(db)
+
+
+def _cached(key, n):
+    """The entry of key, if it is this library's and its variant one of n."""
+    rec = _load().get(key)
+    if (isinstance(rec, dict) and rec.get("library") == library_signature()
+            and 0 <= rec["variant"] < n):
+        return dict(rec, cached=True)
+    return None
+
+
 def context_key(ctx):
     p = ctx.params
     return f"{_device()}|grid|{ctx.nx}x{ctx.ny}|bc{tuple(p.bc)}"
@@ -84,11 +112,10 @@ def tune_context(ctx, f, nsteps=None, reps=3, use_cache=True):
     times.
     Returns {"variant": v, "ms": {variant: ms per step}, "cached": bool}."""
     key = context_key(ctx)
-    db = _load() if use_cache else {}
-    n = lbm.lbm_step_variant_count()
-    if key in db and 0 <= db[key]["variant"] < n:
-        ctx.variant = db[key]["variant"]
-        return dict(db[key], cached=True)
+    hit = _cached(key, lbm.lbm_step_variant_count()) if use_cache else None
+    if hit:
+        ctx.variant = hit["variant"]
+        return hit
     tmp = ctx.empty_f()
     if nsteps is None:
         nsteps = max(3, min(200, int(5e7 / (ctx.nx * ctx.ny))))
@@ -100,9 +127,7 @@ def tune_context(ctx, f, nsteps=None, reps=3, use_cache=True):
     ctx.variant = _pick(ms)
     rec = {"variant": ctx.variant, "ms": {str(k): v for k, v in ms.items()}}
     if use_cache:
-        db = _load()
-        db[key] = rec
-        _store(db)
+        _keep(key, rec)
     return dict(rec, cached=False)
 
 
@@ -110,12 +135,11 @@ def tune_batch(b, f, nsteps=None, slots=(0,), reps=3, use_cache=True):
     """Select the fastest (variant, persistent slots per XCD) for batch b,
     with the same repetition and tie rule as tune_context."""
     key = batch_key(b)
-    db = _load() if use_cache else {}
-    n = lbm.lbm_step_variant_count()
-    if key in db and 0 <= db[key]["variant"] < n:
-        b.variant = db[key]["variant"]
-        b.schedule = (db[key]["slots"], b.schedule[1])
-        return dict(db[key], cached=True)
+    hit = _cached(key, lbm.lbm_step_variant_count()) if use_cache else None
+    if hit:
+        b.variant = hit["variant"]
+        b.schedule = (hit["slots"], b.schedule[1])
+        return hit
     tmp = b.empty_f()
     if nsteps is None:
         nsteps = max(3, min(200, int(5e7 / b.cells)))
@@ -130,9 +154,7 @@ def tune_batch(b, f, nsteps=None, slots=(0,), reps=3, use_cache=True):
     rec = {"variant": b.variant, "slots": b.schedule[0],
            "ms": {f"{v},{q}": t for (v, q), t in ms.items()}}
     if use_cache:
-        db = _load()
-        db[key] = rec
-        _store(db)
+        _keep(key, rec)
     return dict(rec, cached=False)
 
 
@@ -140,11 +162,10 @@ def tune_adjoint(ctx, f, lam, nsteps=None, reps=2, use_cache=True):
     """Select the fastest reverse-step variant for ctx (f, lam: representative
     f^n and lambda^{n+1}); same repetition and tie rule as tune_context."""
     key = context_key(ctx) + "|adjoint"
-    db = _load() if use_cache else {}
-    n = lbm.lbm_adjoint_variant_count()
-    if key in db and 0 <= db[key]["variant"] < n:
-        ctx.adj_variant = db[key]["variant"]
-        return dict(db[key], cached=True)
+    hit = _cached(key, lbm.lbm_adjoint_variant_count()) if use_cache else None
+    if hit:
+        ctx.adj_variant = hit["variant"]
+        return hit
     tmp = ctx.empty_f()
     if nsteps is None:
         nsteps = max(2, min(100, int(2e7 / (ctx.nx * ctx.ny))))
@@ -155,7 +176,5 @@ def tune_adjoint(ctx, f, lam, nsteps=None, reps=2, use_cache=True):
     ctx.adj_variant = _pick(ms)
     rec = {"variant": ctx.adj_variant, "ms": {str(k): v for k, v in ms.items()}}
     if use_cache:
-        db = _load()
-        db[key] = rec
-        _store(db)
+        _keep(key, rec)
     return dict(rec, cached=False)
