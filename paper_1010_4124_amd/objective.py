@@ -78,15 +78,22 @@ class KHIProblem:
     def weight(self, n):
         return self.dt if self.n0 <= n <= self.n1 else 0.0
 
-    def basis(self):
+    def _modes(self):
         if self._basis is None:
             self._basis = inputs.mode_basis(self.nx, self.dx)[0]
         return self._basis
 
+    def basis(self):
+        """The rows of inputs.mode_basis on this grid, read-only: every later run
+        and gradient uses them."""
+        b = self._modes().view()
+        b.flags.writeable = False
+        return b
+
     def fields(self, Dv, Drho, amps):
         return inputs.khi(self.nx, self.ny, self.dx, self.dy, self.dt, self.tau, Dv=float(Dv),
                           Drho=float(Drho), amps=np.asarray(amps, dtype=np.float64),
-                          basis=self.basis(), **self.phys)
+                          basis=self._modes(), **self.phys)
 
     # -- forward ---------------------------------------------------------------
     def run(self, Dv, Drho, amps, keep_checkpoints=True):
@@ -227,7 +234,7 @@ class KHIProblem:
         s = self.fields(Dv, Drho, amps)
         g_rho, g_ux, g_uy, g_T = ctx.init_vjp(*s.fields(), lam)
         t = inputs.khi_tangents(self.nx, self.ny, self.dx, self.dy, float(Dv), float(Drho),
-                                basis=self.basis(),
+                                basis=self._modes(),
                                 **{k: self.phys[k] for k in ("rho1", "rho2", "u0", "p0", "yw")})
         ones = np.ones((1, self.nx))
         dDv = ctx.sep_project(g_ux, ones, t["v"])[0]
