@@ -162,6 +162,12 @@ class KHIProblem:
                     states.append(ctx.step(states[-1], 1))
             yield states, sums
 
+    # gradients on grids below this many cells overlap the recompute by default
+    OVERLAP_MAX_CELLS = 0
+
+    def _overlaps(self, overlap):
+        return self.nx * self.ny < self.OVERLAP_MAX_CELLS if overlap is None else bool(overlap)
+
     def gradient(self, Dv, Drho, amps, ck=None, scale=1.0, overlap=None):
         """(dJ/dD_v, dJ/dD_rho, dJ/da) by the discrete adjoint.
 
@@ -169,14 +175,13 @@ class KHIProblem:
         stream while the current unit's reverse steps run (the two are
         independent); at most one more unit's states and one more segment's
         level-2 checkpoints are alive. The result is the same bit for bit. None (the
-        default): no overlap. Both steps fill the GPU by themselves from 64 x 48
-        cells on (whole-tile kernels, a workgroup or two on every CU), so the
-        second stream only adds its host work and events (us per step of a
-        400-step gradient, overlapped / not: 64 x 48 43 / 32, 256^2 54 / 41,
-        512^2 113 / 110, 1000^2 492 / 432); at 2048^2 the states it frees on one
+        default): overlap below OVERLAP_MAX_CELLS cells only, i.e. nowhere: the
+        overlap was slower on every grid timed (us per step of a 400-step
+        gradient, overlapped / not: 64 x 48 43 / 32, 256^2 54 / 41, 512^2
+        113 / 110, 1000^2 492 / 432), and at 2048^2 the states it frees on one
         stream after use on the other are not reused by torch's caching
-        allocator soon enough either (250 GB reserved for 45 GB in use)."""
-        overlap = bool(overlap)
+        allocator soon enough (250 GB reserved for 45 GB in use)."""
+        overlap = self._overlaps(overlap)
         if ck is None:
             _, ck = self.run(Dv, Drho, amps)
         ctx = self.ctx

@@ -36,3 +36,12 @@ def test_reverse_units_cover_every_step_once_last_first():
         for c0, c1, s0, s1 in units:
             assert c0 <= s0 < s1 <= c1 and s1 - s0 <= sch.K2 and (s0 - c0) % sch.K2 == 0
             assert c0 % sch.K1 == 0 and c1 == min(c0 + sch.K1, N)
+
+
+def test_overlap_threshold_of_the_class():
+    """overlap=None: by OVERLAP_MAX_CELLS, which a caller may raise; nowhere by default."""
+    p = object.__new__(objective.KHIProblem)
+    p.nx, p.ny = 64, 48
+    assert not p._overlaps(None) and p._overlaps(True) and not p._overlaps(False)
+    p.OVERLAP_MAX_CELLS = 64 * 48 + 1
+    assert p._overlaps(None) and not p._overlaps(False)
