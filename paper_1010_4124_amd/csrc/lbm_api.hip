@@ -454,14 +454,15 @@ int lbm_get_step_variant(lbm_ctx* c, int32_t* v)
 //    (1101 x 605 65 against 60, four outflow grids of 600 x 200 59 against 54).
 //  - The fast-tile kernel with its carried sums moves 400 B per cell instead of
 //    310, in rounds of 2048 tiles, and takes some four times as long for a band
-//    tile (one at the grid's edge). On single grids from 4 rounds on it is 2 to
-//    7% ahead where at most one tile in a hundred is a band tile, which takes
-//    an x axis that is periodic and, on all but very large grids, whole tile
-//    columns (fast / whole tiles: 2048 x 1024 183 / 190, 2048 x 1536 270 / 284,
-//    2048^2 356 / 375, 4096^2 1400 / 1500; 0.7% band tiles, 6144 x 1100: 597 / 607),
-//    and behind with more (1.2 and 1.3%, 8200 x 2000 and 6000 x 3000: 1510 / 1487
-//    and 1653 / 1641; 3.1%, 8192 x 256: 222 / 207; 2050^2 466 / 392; a 2048^2 box
-//    552 / 398) and on fewer rounds (1024^2 106 / 97; 1536 x 1024, 3 rounds, 141 / 145).
+//    tile (one at the grid's edge). On single grids from 4 rounds on, with at
+//    most one band tile in 128 (an x axis that is periodic and, on all but very
+//    large grids, whole tile columns), it is ahead or level (shear layers, fast /
+//    whole tiles: 2048 x 1024 164 / 168, 2048 x 1536 239 / 250, 2048^2 316 / 325,
+//    4096^2 1220 / 1284, 3200 x 3000 752 / 742, 6144 x 1100 554 / 533; states that
+//    vary from cell to cell take 10 to 15% longer with both and favour it: 2048^2
+//    356 / 375). It is behind with more (8192 x 800, 1.0%, 558 / 536; 8200 x 2000,
+//    1.2%, 1387 / 1302; 4096 x 512, 1.6%, 177 / 168; a 2048^2 box 552 / 398) and on
+//    fewer rounds (1536 x 1024 129 / 127, 1024^2 97 / 88).
 //    In a batch it is level at best: four grids of 2048^2 1454 / 1462, two 748 / 732,
 //    a 64-instance sweep of 5.3 M cells 468-490 / 449-456.
 int lbmi_tile_rows(int64_t t1, int64_t t2)
@@ -521,7 +522,7 @@ int lbmi_default_variant(int nx, int ny, int bc_xlo)
 {
     constexpr int64_t ROUND = 2048;
     const int64_t tx = ((int64_t)nx + 63) / 64, t4 = tx * (((int64_t)ny + 3) / 4);
-    if (t4 >= 4 * ROUND && 100 * fast_band_tiles(nx, ny, bc_xlo, 4) <= t4)
+    if (t4 >= 4 * ROUND && 128 * fast_band_tiles(nx, ny, bc_xlo, 4) <= t4)
         return variant_index({4, 1, 2, 1, 1, 3});
     return lbmi_default_variant_tiles(tx * ny, tx * (((int64_t)ny + 1) / 2), t4);
 }
