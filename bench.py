@@ -567,7 +567,7 @@ def summarize_batch(trace, log_path, commands):
     ev = _bench_line(log_path, "batch")
     v = ev["variant"]
     nt = "true" if v[4] else "false"
-    name = (f"lbmd::k_step_batch_tile<{v[0]}, {nt}>" if v[5] == 0 and v[1] == 18 else
+    name = (f"lbmd::k_step_batch_tile<{v[0]}, {nt}, false>" if v[5] == 0 and v[1] == 18 else
             f"lbmd::k_step_batch<{v[0]}, {v[1]}, {v[2]}, {v[3]}, {nt}, {v[5]}>")
     step_key = max((k for k in rows if k[0] == name), key=lambda k: int(rows[k][2]))
     red_key = next(k for k in rows if k[0] == "lbmd::k_reduce_batch")
@@ -620,12 +620,12 @@ def counter_table(root, match):
 # ---------------------------------------------------------------------------
 def pmc_run(args):
     """A short run for one rocprofv3 counter pass: the tuned main step (with
-    --only adjoint: ten 2048^2 reverse steps of variant --variant, else of
-    the context's default) and a plain device copy of COPY_BYTES."""
+    --only adjoint: ten reverse steps at --n (2048)^2 of variant --variant, else
+    of the context's default) and a plain device copy of COPY_BYTES."""
     import torch
     from paper_1010_4124_amd import inputs, lbm, tune
     if args.only == "adjoint":
-        s = inputs.khi(2048, 2048, Dv=0.01, Drho=0.04)
+        s = inputs.khi(args.n, args.n, Dv=0.01, Drho=0.04)
         ctx = lbm.Context.from_setup(s)
         f0 = ctx.init(*s.fields())
         if args.variant is not None:
@@ -811,7 +811,8 @@ def main():
     ap.add_argument("--commands", nargs="*")
     ap.add_argument("--sq", nargs="*", help="SQ counter-pass directories for --summarize")
     ap.add_argument("--n", type=int, default=MAIN_N,
-                    help="--summarize: the side of the profiled grid (2048, or 512 for forward512)")
+                    help="the side of the profiled grid: --summarize (2048, or 512 for forward512), "
+                         "--pmc-run --only adjoint")
     ap.add_argument("--last", type=int, default=20,
                     help="--summarize: dispatches of the timed call (its last ones)")
     ap.add_argument("--only", choices=("forward512", "batch", "adjoint"))

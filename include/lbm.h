@@ -137,8 +137,10 @@ int lbm_sums(lbm_ctx* ctx, const double* f, double* sums, lbm_stream stream);
  * step reads sums_in instead of forming them from f_in and writes sums_out
  * as it writes f_out (lbm_sums of f_out up to rounding; bit for bit for the
  * fast-tile variants, mode 3, which sum in lbm_sums's order); with the
- * others sums_out is lbm_sums of f_out. f_out is lbm_step's result bit for
- * bit when sums_in is lbm_sums(f_in).
+ * others sums_out is lbm_sums of f_out. Where a whole-tile variant (mode 0 with
+ * G = 18) is set, grids of 2^21 cells or more take the fast-tile kernel here,
+ * which needs no pass for the sums; its results are the same bit for bit.
+ * f_out is lbm_step's result bit for bit when sums_in is lbm_sums(f_in).
  * For a sequence of single steps whose sums feed lbm_adjoint_step_sums.
  * Outputs must not overlap the inputs or each other. */
 int lbm_step_sums(lbm_ctx* ctx, const double* f_in, const double* sums_in, double* f_out,
@@ -208,8 +210,9 @@ int lbm_adjoint_step_sums(lbm_ctx* ctx, const double* f_n, const double* sums_n,
  * PS): tiles of 64 x R cells, the 18 moving velocities split into G groups
  * (one workgroup per tile and group; G = 18 with PS = 0: one workgroup of 12
  * wavefronts takes all velocities of a tile, f_n and lam_np1 read once), W the
- * wavefronts-per-SIMD target, and PS = 1 when a per-cell pass first forms the equilibrium/objective terms
- * and the rest plane (then the context's [4][ny][nx] buffer holds them);
+ * wavefronts-per-SIMD target, and PS = 1 when a per-cell pass first forms the
+ * equilibrium/objective terms and the rest plane (then the context's
+ * [4][ny][nx] buffer holds them);
  * PS = 2: the same pass, then one workgroup per moving velocity marches
  * along y over 64-column strips in chunks of R rows, each face evaluated
  * once, the tiles next to non-periodic sides as PS = 1 with R = 4.
@@ -251,8 +254,8 @@ int lbm_sep_project(lbm_ctx* ctx, const double* g, const double* A, int32_t M, c
  * being computed; NT = 1 stores f^{n+1} with non-temporal stores. M says how
  * a tile obtains its moments (Eq. (10)):
  *   0  every (tile, group) workgroup sums the 19 planes of f^n itself; with
- *      G = 18 one workgroup of 12 wavefronts takes all velocities of a tile,
- *      each plane read once;
+ *      G = 18 one workgroup of 12 wavefronts (R = 4: 8) takes all velocities
+ *      of a tile, each plane read once;
  *   1  the sums rho, j, E are carried from each step to the next (a call
  *      first forms them from f_in) and the G groups are the waves of one
  *      workgroup;
@@ -267,7 +270,9 @@ int lbm_sep_project(lbm_ctx* ctx, const double* g, const double* A, int32_t M, c
  * evaluates the same formulas; results agree to rounding (the WENO face
  * arithmetic is grouped per strip of R cells and the moment sums per wave),
  * and a given variant is deterministic. lbm_set_step_variant selects the
- * variant that later lbm_step calls of that context launch. */
+ * variant that later lbm_step calls of that context launch (lbm_step_sums: see
+ * there for the whole-tile variants). Contexts with another scheme than WENO5
+ * have kernels of their own. */
 int lbm_step_variant_count(void);
 int lbm_step_variant_info(int32_t variant, int32_t* info6);
 int lbm_set_step_variant(lbm_ctx* ctx, int32_t variant);

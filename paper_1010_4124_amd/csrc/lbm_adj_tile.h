@@ -17,10 +17,11 @@
 // so what plane j's wall faces give those ghosts belongs to i. The wave of j has
 // it in its strip already and hands it over through LDS.
 //
-// What bounds it: the face arithmetic (3.25 faces per cell and velocity, ~100
-// operations each: ~10 us of a tile's ~18) and, with one workgroup per CU
-// (142 KB of LDS, 168 registers), the phases that do not overlap. Measured per
-// reverse step, against the state pass and one workgroup per tile and velocity:
+// What bounds it: one workgroup per CU (142 KB of LDS, 168 registers), whose
+// phases do not overlap: VALU issues 43% of the time at 256^2 (9 of 21 us, most of
+// it the 3.25 faces per cell and velocity) and 52% at 2048^2, with HBM traffic
+// of 498 and 476 B per cell of the 456 it cannot do without. Measured per reverse
+// step, against the state pass and one workgroup per tile and velocity:
 // 128^2 19 us (27), 256^2 21 us (40), 600 x 200 37 us (68).
 #pragma once
 

@@ -509,7 +509,8 @@ int lbmi_default_variant_tiles(int64_t t1, int64_t t2, int64_t t4)
 // The variant of lbm_step_sums: a whole-tile step is followed by a pass that
 // forms the sums of its result (184 B per cell), so from 2^21 cells on the
 // fast-tile kernel, which writes them with the state, takes its place (2048^2:
-// 320 us against 309 + 160; results are the same bit for bit).
+// 320 us against 325 + 160, a box of that size 552 against 398 + 160; results are
+// the same bit for bit).
 int lbmi_sums_variant(int v, int64_t cells)
 {
     int d[6];

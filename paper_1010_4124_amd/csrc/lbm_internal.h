@@ -71,8 +71,8 @@ hipError_t launch_step(int variant, const double* fin, double* fout, const Const
 // one step of an upwind scheme in tiles of 64 x R cells (R = 1, 2 or 4), energy
 // partials per tile, or (R = 0) by one thread per cell, partials per 256 cells
 hipError_t launch_step_lo(int scheme, int R, const double* fin, double* fout, const Consts& k,
-                          double* ke_part, int nx, int ny, const int bc[4], double cx, double cy, double ct, int ke_axis,
-                          const double* const gb[4], hipStream_t st);
+                          double* ke_part, int nx, int ny, const int bc[4], double cx, double cy,
+                          double ct, int ke_axis, const double* const gb[4], hipStream_t st);
 hipError_t launch_outflow(const double* f, int nx, int ny, double* const g[4], const Consts& k,
                           hipStream_t st);
 hipError_t launch_sums(const double* f, double* m, const Consts& k, int64_t n, hipStream_t st);

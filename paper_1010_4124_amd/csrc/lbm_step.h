@@ -619,7 +619,7 @@ __device__ __forceinline__ void step_work(const StepGrid& a, const Consts& k, SE
 // refuses one that does): the targets are chosen so that none does. The
 // PH_TILE entries (reported as M = 0 with G = 18: they sum the planes of f^n
 // themselves, every velocity of a tile in one workgroup) always have a target
-// of 6 wavefronts per SIMD, two workgroups of 12 per CU.
+// of 6 wavefronts per SIMD: two workgroups of 12 per CU, or three of 8 (R = 4).
 #define LBM_STEP_VARIANTS(X)                                                                     \
     X(4, 1, 3, 1, 0, 0, 2) X(4, 3, 3, 1, 0, 0, 2) X(8, 2, 2, 1, 0, 0, 1)                         \
     X(8, 1, 2, 1, 0, 0, 1) X(2, 3, 4, 1, 0, 0, 3) X(8, 2, 2, 1, 1, 0, 1)                         \

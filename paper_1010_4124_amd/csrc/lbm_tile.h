@@ -31,9 +31,9 @@
 // What bounds it: on small grids the latency of one tile (launch, loads,
 // faces, stores in sequence), hence the many waves and the low R; on large
 // ones the phases of the workgroups that fit a CU overlap incompletely: with
-// the three of tile8_step (R = 4) VALU is busy 69% of the time at 2048^2, with
-// HBM traffic of 310 B per cell of the 304 it cannot do without (the fast-tile
-// kernel: 408). Measured per step, against the state pass and plane kernel it
+// the three of tile8_step (R = 4) VALU issues 63 to 68% of the time at 2048^2, with
+// HBM traffic of 313 B per cell of the 304 it cannot do without (the fast-tile
+// kernel: 60% and 399). Measured per step, against the state pass and plane kernel it
 // replaces: 400 x 4 6.1 us (12.6), 256^2 10.4 (17.0), 512^2 25.2 (37.0),
 // 1101 x 605 60 (101), four outflow grids of 600 x 200 in a batch 54 (76).
 #pragma once
@@ -565,9 +565,9 @@ __device__ __forceinline__ void tile_step(const Grid& g, const TileConsts& k, do
 // three plane loads, and a wave of each kind shares a SIMD. The x faces come
 // after the second barrier, one velocity at a time, to stay within 80
 // registers. Per step against 12 waves: 512^2 25.9 us (27.1), 1101 x 605 62.4
-// (66.4), 1024^2 86 (100), 1448^2 175 (196), 2048^2 309 (358; 4.2 TB/s, VALU
-// busy 69%), a batch of 1.45 M cells 167 (180); below one round, where only a
-// tile's latency counts, 600 x 200 24.1-24.7 (24.3).
+// (66.4), 1024^2 86 (100), 1448^2 175 (196), 2048^2 309 (358), a
+// batch of 1.45 M cells 167 (180); below one round, where only a tile's latency
+// counts, 600 x 200 24.1-24.7 (24.3).
 // Raised wave priority around the loads gives 6% at 1101 x 605 (66.2 to 62.4)
 // and 5% on four grids of 600 x 200, but costs as much on the states beyond the
 // cache (2048^2 309 to 325), which are the ones stored non-temporally.
@@ -579,7 +579,6 @@ __device__ __forceinline__ void tile8_step(const Grid& g, const TileConsts& k, d
     using S = TileWg<R>;
     constexpr int ROWS = R + 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int t = wave & 3;
     const TileVel va = vel_y(wave < 4 ? 0 : 2, wave & 3);
     const int jn = wave == 5 ? 2 : wave == 6 ? 4 : wave == 7 ? 5 : 0;
     const TileVel yb = vel_y(1, wave & 3), nb = vel_x(jn), vb = wave < 4 ? yb : nb;
@@ -678,7 +677,6 @@ __device__ __forceinline__ void tile8_step(const Grid& g, const TileConsts& k, d
         finish(vc, z);
     }
 }
-
 
 template <int R, bool NT, bool FAST, int SCHEME, class Grid>
 __device__ __forceinline__ void tile_step_any(const Grid& g, const TileConsts& k, double* lds)
