@@ -15,7 +15,8 @@
 //   phase B  output rows
 // Reflecting walls in y: the ghost rows of plane j hold rows of its mirror i,
 // so what plane j's wall faces give those ghosts belongs to i. The wave of j has
-// it in its strip already and hands it over through LDS.
+// it in its strip already and hands it over through LDS. The terms of walls in x
+// are added by a second kernel (k_adj_wall).
 //
 // What bounds it: one workgroup per CU (142 KB of LDS, 168 registers), whose
 // phases do not overlap: VALU issues 43% of the time at 256^2 (9 of 21 us, most of
@@ -105,8 +106,9 @@ __device__ __forceinline__ void adj_tile_step(const AdjArgs& a, int x0, int y0, 
     const bool hasm = v.m >= 0 && v.m < R;
     const GridBC b = grid_of(a);
     const Consts& k = a.k;
-    double* const s_fy = lds + (v.iy - 1) * S::PL + S::FC;
-    double* const s_fn = lds + (v.in - 1) * S::PL + S::FC;
+    // (uniform: the compiler would keep them in vector registers, and spill)
+    double* const s_fy = lds + (int)uniform((v.iy - 1) * S::PL) + S::FC;
+    double* const s_fn = lds + (int)uniform((v.in - 1) * S::PL) + S::FC;
 
     double f0 = 0.0, l0 = 0.0;
     // the rest plane of the wave's cell row (boundary tiles: asked for after the
@@ -359,42 +361,34 @@ __device__ __forceinline__ void adj_tile_step(const AdjArgs& a, int x0, int y0, 
         for (int j = 0; j < R; ++j) lq[j] = s_fn[S::LAM + j * S::P + (v.nnegx ? 63 - lane : lane)];
     }
     __syncthreads();
-    // Wall terms that no strip has: those of reflecting walls in x, and of the
-    // one row whose ghost beyond a wall in y is past the tile's strip. They
-    // wait in the place of the wave's lambda planes.
-    const int gx = x0 + lane;
-    const bool wxlo = !FAST && b.bc[XLO] == REFLECT && x0 < HALO;
-    const bool wxhi = !FAST && b.bc[XHI] == REFLECT && x0 + 64 > nx - HALO;
-    const bool extra = !FAST && (wxlo || wxhi || (whi && H == R + 2));
+    // The third ghost row beyond a wall in y whose last tile has two rows is past
+    // the strip of the tile below it: its one face that reaches row ny - 3, for
+    // the velocities towards the wall. It waits in the place of the lambda plane.
+    const bool past = !FAST && whi && H == R + 2 && !v.negy;
     if constexpr (!FAST) {
-        if (extra) {
-#pragma unroll 1
-            for (int n = 0; n < (v.hasn ? 2 * R : R); ++n) {
-                const int m = n % R, i = n < R ? v.iy : v.in, gy = y0 + m;
-                double e = 0.0;
-#pragma unroll 1
-                for (int side = 0; side < 3; ++side) {
-                    const int p = side == 0 ? gx : side == 1 ? nx - 1 - gx : H - 1 - m;
-                    const bool on = side == 0   ? wxlo
-                                    : side == 1 ? wxhi
-                                                : whi && 2 * H - 1 - m > R + 3;
-                    if (!on || p >= HALO || lane >= w || gy >= ny) continue;
-                    const int j = side < 2 ? k.mirx[i] : k.miry[i];
-                    const double vj = side < 2 ? k.vx[j] : k.vy[j];
-                    e += wall_term(a, j, side == 0 ? 0 : side == 1 ? nx - 1 : gx,
-                                   side < 2 ? gy : ny - 1, side == 0 ? 1 : side == 1 ? -1 : 0,
-                                   side < 2 ? 0 : -1, p, side == 0 ? vj : -vj,
-                                   side < 2 ? a.cx : a.cy);
-                }
-                (n < R ? s_fy : s_fn)[S::LAM + m * S::P + lane] = e;
-            }
+        if (past) {
+            const int i = (int)uniform(v.iy), j = k.miry[i];
+            const unsigned l8 = 8u * (unsigned)tile_lane();
+            int last = ny - 1;
+            asm volatile("" : "+s"(last));  // (no addresses kept from the tile's loads)
+            auto at = [&](const double* base, int pl, int up) {
+                return row_load(rows_rsrc(base + pl * plane + (int64_t)(last - up) * nx + x0, 8 * w),
+                                l8, 0);
+            };
+            double F[5] = {at(a.f, i, 2), at(a.f, i, 1), at(a.f, i, 0), at(a.f, j, 0),
+                           at(a.f, j, 1)};
+            const double mu = a.cy * at(a.lam1, j, 0);
+#pragma unroll
+            for (int q = 0; q < 5; ++q) F[q] *= vy;
+            double G[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+            weno_face_bar(F, eps, mu, G);
+            s_fy[S::LAM + lane] = vy * G[0];
         }
     }
 
     // ---- phase B
     const double omct = 1.0 - a.ct;
-    auto put = [&](const double* s_p, int plane_i, int m_, double l, double x, double y, double ux,
-                   double uy) {
+    auto put = [&](int plane_i, int m_, double l, double x, double y, double ux, double uy) {
         const int i = (int)uniform(plane_i), m = (int)uniform(m_);
         const double* sk = lds + S::K + m * 64 + lane;
         double out = __builtin_fma(omct, l, sk[0]);
@@ -402,7 +396,7 @@ __device__ __forceinline__ void adj_tile_step(const AdjArgs& a, int x0, int y0, 
         out = __builtin_fma(sk[2 * R * 64], uy, out);
         out = __builtin_fma(sk[3 * R * 64], k.hv2[i], out);
         out += __builtin_fma(ux, x, y);
-        if (extra) out += s_p[S::LAM + m * S::P + lane];
+        if (past && i == v.iy && m == R - 1) out += s_fy[S::LAM + lane];
         row_store<false>(out, rows_rsrc(a.lam0 + i * plane + (int64_t)(y0 + m) * nx + x0,
                                         FAST || y0 + m < ny ? 8 * w : 0),
                          8u * (unsigned)lane, 0);
@@ -413,11 +407,11 @@ __device__ __forceinline__ void adj_tile_step(const AdjArgs& a, int x0, int y0, 
         double y = accy[mc];
         // (from the wave of the velocity mirrored in y)
         if (wlo || whi) y += lds[S::W + (wave ^ 3) * R * 64 + m * 64 + lane];
-        put(s_fy, v.iy, m, lc[mc], xy[mc], y, vx, vy);
+        put(v.iy, m, lc[mc], xy[mc], y, vx, vy);
     }
     if (v.hasn) {
 #pragma unroll
-        for (int m = 0; m < R; ++m) put(s_fn, v.in, m, lq[m], xn[m], 0.0, vn, 0.0);
+        for (int m = 0; m < R; ++m) put(v.in, m, lq[m], xn[m], 0.0, vn, 0.0);
     }
 }
 
@@ -435,6 +429,33 @@ void k_adj_tile(AdjArgs a)
         adj_tile_step<R, true>(a, tx * TX, ty * R, lds);
     else
         adj_tile_step<R, false>(a, tx * TX, ty * R, lds);
+}
+
+// The wall terms of reflecting walls in x, which no strip of k_adj_tile has, added
+// to lam0: the three columns next to each, a thread per cell (plane, row, column).
+// Inside the tile kernel, as its last chain of loads and faces, these took 88 of
+// the 107 us of a 64 x 64 box; so the two kernels take 26 (256 x 195: 48, 29).
+// Columns next to the walls of a grid that has any.
+__host__ __device__ inline int adj_wall_columns(int nx, int bc_xlo, int bc_xhi)
+{
+    const bool lo = bc_xlo == REFLECT, hi = bc_xhi == REFLECT;
+    return lo && hi ? min(2 * HALO, nx) : lo || hi ? HALO : 0;
+}
+
+__global__ __launch_bounds__(64) void k_adj_wall(AdjArgs a)
+{
+    const bool lo = a.bc[XLO] == REFLECT, hi = a.bc[XHI] == REFLECT;
+    const int nc = adj_wall_columns(a.nx, a.bc[XLO], a.bc[XHI]);
+    const int64_t t = (int64_t)blockIdx.x * 64 + threadIdx.x, rows = t / nc;
+    if (rows >= (int64_t)(NV - 1) * a.ny) return;
+    const int i = 1 + (int)(rows / a.ny), y = (int)(rows - (int64_t)(i - 1) * a.ny);
+    const int c = (int)(t - rows * nc), x = lo && c < HALO ? c : a.nx - nc + c;
+    const int j = a.k.mirx[i];
+    double e = 0.0;  // (a cell may be near both walls)
+    if (lo && x < HALO) e += wall_term(a, j, 0, y, 1, 0, x, a.k.vx[j], a.cx);
+    if (hi && x >= a.nx - HALO)
+        e += wall_term(a, j, a.nx - 1, y, -1, 0, a.nx - 1 - x, -a.k.vx[j], a.cx);
+    a.lam0[((int64_t)i * a.ny + y) * a.nx + x] += e;
 }
 
 }  // namespace lbmd
