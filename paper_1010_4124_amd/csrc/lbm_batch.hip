@@ -218,16 +218,15 @@ __global__ __launch_bounds__(256) void k_state_batch(const double* __restrict__ 
 
 // Outflow ghosts of every outflow side of a batch in one launch: entry b of
 // oflow is (instance, side + 4 * block along the side).
-__global__ __launch_bounds__(256) void k_outflow_batch(const double* __restrict__ fin,
-                                                       const int2* __restrict__ oflow,
-                                                       const BatchInst* __restrict__ inst,
-                                                       double* gbuf, Consts k)
+__global__ __launch_bounds__(OUTFLOW_BLOCK) void k_outflow_batch(
+    const double* __restrict__ fin, const int2* __restrict__ oflow,
+    const BatchInst* __restrict__ inst, double* gbuf, Consts k)
 {
     const int2 e = oflow[blockIdx.x];
     const BatchInst& d = inst[e.x];
     const int side = e.y & 3;
     outflow_point(fin + d.off, d.nx, d.ny, gbuf + d.goff[side], side,
-                  (e.y >> 2) * 256 + (int)threadIdx.x, k);
+                  (e.y >> 2) * OUTFLOW_BLOCK + (int)threadIdx.x, k);
 }
 
 __global__ __launch_bounds__(256) void k_reduce_batch(const double* __restrict__ part,
@@ -417,8 +416,8 @@ hipError_t launch_batch_step(lbm_batch* b, const double* src, double* dst, bool 
     // outflow ghosts of the state this step starts from, all instances at
     // once (with a state pass, that pass writes them)
     if (b->noflow > 0 && V.M != PH_STATE) {
-        hipLaunchKernelGGL(k_outflow_batch, dim3((unsigned)b->noflow), dim3(256), 0, st, src,
-                           b->oflow, b->inst, b->gbuf, b->k);
+        hipLaunchKernelGGL(k_outflow_batch, dim3((unsigned)b->noflow), dim3(OUTFLOW_BLOCK), 0, st,
+                           src, b->oflow, b->inst, b->gbuf, b->k);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -678,7 +677,8 @@ static int batch_create_impl(const lbm_params* inst, int32_t n, const int64_t* f
         for (int sd = 0; sd < 4; ++sd) {
             if (d.goff[sd] < 0) continue;
             const int len = sd < 2 ? d.ny : d.nx;
-            for (int q = 0; q < (len + 255) / 256; ++q) ofl.push_back(make_int2(i, sd + 4 * q));
+            for (int q = 0; q < (len + OUTFLOW_BLOCK - 1) / OUTFLOW_BLOCK; ++q)
+                ofl.push_back(make_int2(i, sd + 4 * q));
         }
     }
     b->nblk = (int)blk.size();

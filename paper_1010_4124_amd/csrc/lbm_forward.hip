@@ -207,13 +207,13 @@ __global__ void k_side_eq(double* out, double4 s0, double4 s1, double4 s2, doubl
 }
 
 // Outflow ghosts of one grid (outflow_point), blockIdx.y = side.
-__global__ __launch_bounds__(256) void k_outflow(const double* __restrict__ f, int nx, int ny,
-                                                 double* g0, double* g1, double* g2, double* g3,
-                                                 Consts k)
+__global__ __launch_bounds__(OUTFLOW_BLOCK) void k_outflow(const double* __restrict__ f, int nx,
+                                                           int ny, double* g0, double* g1,
+                                                           double* g2, double* g3, Consts k)
 {
     const int side = blockIdx.y;
     double* g = side == 0 ? g0 : side == 1 ? g1 : side == 2 ? g2 : g3;
-    if (g) outflow_point(f, nx, ny, g, side, blockIdx.x * 256 + threadIdx.x, k);
+    if (g) outflow_point(f, nx, ny, g, side, blockIdx.x * OUTFLOW_BLOCK + threadIdx.x, k);
 }
 
 // Moments of Eq. (10) per cell.
@@ -472,8 +472,8 @@ hipError_t launch_outflow(const double* f, int nx, int ny, double* const g[4], c
                           hipStream_t st)
 {
     const int len = nx > ny ? nx : ny;
-    hipLaunchKernelGGL(k_outflow, dim3((len + 255) / 256, 4), dim3(256), 0, st, f, nx, ny, g[0],
-                       g[1], g[2], g[3], k);
+    hipLaunchKernelGGL(k_outflow, dim3((len + OUTFLOW_BLOCK - 1) / OUTFLOW_BLOCK, 4),
+                       dim3(OUTFLOW_BLOCK), 0, st, f, nx, ny, g[0], g[1], g[2], g[3], k);
     return hipGetLastError();
 }
 
