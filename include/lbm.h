@@ -209,7 +209,8 @@ int lbm_adjoint_step_sums(lbm_ctx* ctx, const double* f_n, const double* sums_n,
 /* Reverse-step variants (same role as the step variants). info4 = (R, G, W,
  * PS): tiles of 64 x R cells, the 18 moving velocities split into G groups
  * (one workgroup per tile and group; G = 18 with PS = 0: one workgroup of 12
- * wavefronts takes all velocities of a tile, f_n and lam_np1 read once), W the
+ * wavefronts takes all velocities of a tile, f_n and lam_np1 read once, and next
+ * to reflecting walls in x a second launch adds their terms), W the
  * wavefronts-per-SIMD target, and PS = 1 when a per-cell pass first forms the
  * equilibrium/objective terms and the rest plane (then the context's
  * [4][ny][nx] buffer holds them);

@@ -19,7 +19,7 @@
 // are added by a second kernel (k_adj_wall).
 //
 // What bounds it: one workgroup per CU (142 KB of LDS, 168 registers), whose
-// phases do not overlap: VALU issues 43% of the time at 256^2 (9 of 21 us, most of
+// phases do not overlap: VALU issues 41% of the time at 256^2 (9 of 22 us, most of
 // it the 3.25 faces per cell and velocity) and 52% at 2048^2, with HBM traffic
 // of 498 and 476 B per cell of the 456 it cannot do without. Measured per reverse
 // step, against the state pass and one workgroup per tile and velocity:
