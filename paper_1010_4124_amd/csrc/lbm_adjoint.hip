@@ -1317,8 +1317,9 @@ hipError_t launch_adjoint(int variant, const double* f, const double* sums, cons
         a.per_xcd = (a.nwork + 7) / 8;
         hipLaunchKernelGGL(V.kernel, dim3(8 * a.per_xcd), dim3(64 * TILE_WAVES), 0, st, a);
         const int64_t cells = (int64_t)adj_wall_columns(nx, bc[XLO], bc[XHI]) * (NV - 1) * ny;
-        if (cells > 0)
-            hipLaunchKernelGGL(k_adj_wall, dim3((unsigned)((cells + 63) / 64)), dim3(64), 0, st, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || cells == 0) return e;
+        hipLaunchKernelGGL(k_adj_wall, dim3((unsigned)((cells + 63) / 64)), dim3(64), 0, st, a);
         return hipGetLastError();
     }
     if (V.PS) {
